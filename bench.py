@@ -35,23 +35,23 @@ ORDER = 100
 DX = 1.0
 DT = 0.5
 PASSES = ("x_fwd_fill", "y_fwd", "z_push", "y_inv", "x_inv_merge")
-# Kernels of each pass: the run-time-schedule kernel, or the one compiled for the two-stage
-# line schedule (the plan reports which one each pass uses).
-KERNELS = {"x_fwd_fill": ("k_xfwd", "k_xfwd2"), "y_fwd": ("k_ypass<-1>", "k_ypass2<-1>"),
-           "z_push": ("k_zpush", "k_zpush2"), "y_inv": ("k_ypass<1>", "k_ypass2<1>"),
-           "x_inv_merge": ("k_xinv", "k_xinv2")}
+# Kernels of each pass: the Stockham kernel, or the radix-pair kernel (the plan reports which
+# one each pass uses).
+KERNELS = {"x_fwd_fill": ("k_xfwd", "k_pxfwd"), "y_fwd": ("k_ypass<-1>", "k_pypass<-1>"),
+           "z_push": ("k_zpush", "k_pzpush"), "y_inv": ("k_ypass<1>", "k_pypass<1>"),
+           "x_inv_merge": ("k_xinv", "k_pxinv")}
 
 
 def pass_of_kernel(name):
     """The step pass a single-box pass kernel belongs to (None for other kernels)."""
     import re
 
-    m = re.search(r"k_(xfwd|ypass|zpush|xinv)(2?)(_b)?<(-?1)?", name)
-    if not m or m.group(3):
+    m = re.search(r"k_p?(xfwd|ypass|zpush|xinv)(_b)?<(-?1)?", name)
+    if not m or m.group(2):
         return None
     kind = m.group(1)
     if kind == "ypass":
-        return "y_fwd" if m.group(4) == "-1" else "y_inv"
+        return "y_fwd" if m.group(3) == "-1" else "y_inv"
     return {"xfwd": "x_fwd_fill", "zpush": "z_push", "xinv": "x_inv_merge"}[kind]
 
 
@@ -116,7 +116,8 @@ def source_digest():
     import re
 
     h = hashlib.sha256()
-    for name in ("passes.hip", "fft_lds.hpp", "cplx.hpp", "internal.hpp", "gmem.hpp"):
+    for name in ("passes.hip", "pair_passes.hpp", "pass_common.hpp", "pair_fft.hpp", "fft_lds.hpp", "cplx.hpp",
+                 "internal.hpp", "gmem.hpp"):
         with open(os.path.join(ROOT, "paper_1812_07357_amd", "csrc", name)) as f:
             text = f.read()
         text = re.sub(r"/\*.*?\*/", " ", text, flags=re.S)
@@ -149,7 +150,7 @@ def run_gpu(precision, inputs_host, steps, warmup, staggered=False):
                       staggered=staggered)
     plan.autotune()
     schedule = {"xyz"[a]: plan.schedule(a) for a in range(3)}
-    schedule["two_stage_passes"] = [PASSES[i] for i in range(5) if (plan.query(psatd.Q_TWO_STAGE) >> i) & 1]
+    schedule["pair_passes"] = [PASSES[i] for i in range(5) if (plan.query(psatd.Q_TWO_STAGE) >> i) & 1]
     g1 = torch.as_tensor(inputs_host, dtype=dtype).to("cuda")
     origin = (0, 0, 0)
     for _ in range(warmup):

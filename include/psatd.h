@@ -158,9 +158,9 @@ enum {
   PSATD_Q_WORKSPACE_BYTES = 4,  /* device bytes owned by the plan */
   PSATD_Q_SPECTRUM_POINTS = 5,  /* (box_x/2+1) * box_y * box_z */
   PSATD_Q_Z_COLUMNS = 6,        /* (kx, ky) columns per tile of the k-space pass */
-  PSATD_Q_TWO_STAGE = 7         /* bit i set: pass i+1 of the step runs a kernel compiled for its
-                                   two-stage line schedule (x forward, y forward, k-space, y inverse,
-                                   x inverse); the autotuner keeps the faster kernel per pass */
+  PSATD_Q_TWO_STAGE = 7         /* bit i set: pass i+1 of the step (x forward, y forward, k-space, y inverse,
+                                   x inverse) runs the two-stage kernel of its line's radix pair, otherwise
+                                   the Stockham kernel */
 };
 int psatd_plan_query(const psatd_plan* plan, int what, long long* value);
 
@@ -175,8 +175,8 @@ int psatd_plan_tables(const psatd_plan* plan, void* dst, void* stream);
 
 /* Schedule autotuner.  For each axis, times the passes that transform along
  * it (x: first and last pass, y: second and fourth, z: the k-space pass) for
- * several radix factorisations / orders of the line length and several tile
- * sizes on the plan's own workspace, and keeps the fastest.  Results are cached
+ * several radix pairs (axes on the Stockham kernels: factorisations, orders and tile
+ * sizes) of the line length on the plan's own workspace, and keeps the fastest.  Results are cached
  * per (precision, axis, length, other box lengths): in memory for the process,
  * and in the JSON file `cache_path` if it is not NULL (read first, rewritten
  * after).  Synchronises `stream`.  Results of later steps are unchanged up to

@@ -27,19 +27,25 @@ HIPCC = os.environ.get("HIPCC", shutil.which("hipcc") or "/opt/rocm/bin/hipcc")
 FLAGS = [
     "-O3", "-std=c++17", "-fPIC", f"--offload-arch={ARCH}",
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
+    # -0 and +0 are the same field value: zero padding folds out of the chirp-z butterflies
+    "-fno-signed-zeros",
     "-Wall", "-Wno-unused-function",
     f"-I{os.path.join(ROOT, 'include')}",
 ]
 
-# (source, object name, extra flags).  passes.hip is compiled once per
-# (pass, precision) unit, the run-time z kernels in four units, so that the large pass
-# kernels build in parallel.
-_PASS_UNITS = [(u, name, prec) for u, name in ((1, "xfwd"), (2, "ypass"), (3, "zpush"), (4, "zpush_batch"),
-                                               (5, "xinv"), (6, "zpush_two_stage"), (7, "zpush_multi"),
-                                               (8, "zpush_pml"), (9, "zpush_pml_multi"))
+# (source, object name, extra flags).  passes.hip is compiled once per unit and precision, the
+# pair kernels (units 7..9) also once per pass, so that the large pass kernels build in
+# parallel; the slowest units come first.
+_PASS_UNITS = [(u, part, f"{name}_{kind}", prec)
+               for part, name in ((3, "zpush"), (2, "ypass"), (1, "xfwd"), (4, "xinv"))
+               for u, kind in ((7, "pair"), (9, "pair_batch"), (8, "chirp"))
                for prec in ("float", "double")]
-SOURCES = [("passes.hip", f"passes_{name}_{prec}", [f"-DPSATD_UNIT={u}", f"-DPSATD_REAL={prec}"])
-           for u, name, prec in _PASS_UNITS]
+_PASS_UNITS += [(u, 0, name, prec)
+                for u, name in ((1, "xfwd"), (2, "ypass"), (3, "zpush"), (4, "zpush_batch"), (5, "xinv"), (6, "zpush_pml"))
+                for prec in ("float", "double")]
+SOURCES = [("passes.hip", f"passes_{name}_{prec}",
+            [f"-DPSATD_UNIT={u}", f"-DPSATD_REAL={prec}"] + ([f"-DPSATD_PART={part}"] if part else []))
+           for u, part, name, prec in _PASS_UNITS]
 SOURCES += [(src, os.path.splitext(src)[0], []) for src in ("tables.hip", "guards.hip", "plan.hip", "mlp.hip", "pic.hip", "pml.hip")]
 
 

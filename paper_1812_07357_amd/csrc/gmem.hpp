@@ -55,8 +55,15 @@ struct gm<float> {
   static __device__ __forceinline__ cx<float> ldc_s(rsrc_t r, uint32_t i, uint32_t so) {
     return __builtin_bit_cast(cx<float>, __builtin_amdgcn_raw_buffer_load_b64(r, i * 8u, (int)so, 0));
   }
-  static __device__ __forceinline__ void stc_s(rsrc_t r, uint32_t i, uint32_t so, cx<float> v) {
-    __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, v), r, i * 8u, (int)so, 0);
+  // the same for a store, dropped unless `ok`
+  static __device__ __forceinline__ void stc_if(rsrc_t r, bool ok, uint32_t i, uint32_t so, cx<float> v) {
+    __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, v), r, ok ? i * 8u : 0xfffffff8u, (int)so, 0);
+  }
+  // complex elements i and i + 1 in one 16-byte load (8-byte aligned)
+  static __device__ __forceinline__ void ldc2(rsrc_t r, uint32_t i, cx<float>& a, cx<float>& b) {
+    const u32x4 w = __builtin_amdgcn_raw_buffer_load_b128(r, i * 8u, 0, 0);
+    a = {__uint_as_float(w[0]), __uint_as_float(w[1])};
+    b = {__uint_as_float(w[2]), __uint_as_float(w[3])};
   }
   // complex elements i and i + 1 in one 16-byte store
   template <int P = kKeep>
@@ -87,11 +94,19 @@ struct gm<double> {
     stc<P>(r, i, a);
     stc<P>(r, i + 1u, b);
   }
+  static __device__ __forceinline__ void ldc2(rsrc_t r, uint32_t i, cx<double>& a, cx<double>& b) {
+    a = ldc(r, i);
+    b = ldc(r, i + 1u);
+  }
   static __device__ __forceinline__ cx<double> ldc_s(rsrc_t r, uint32_t i, uint32_t so) {
     return __builtin_bit_cast(cx<double>, __builtin_amdgcn_raw_buffer_load_b128(r, i * 16u, (int)so, 0));
   }
-  static __device__ __forceinline__ void stc_s(rsrc_t r, uint32_t i, uint32_t so, cx<double> v) {
-    __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, v), r, i * 16u, (int)so, 0);
+  // The offset goes into the vector address here: with a scalar-register offset the compiler
+  // leaves out the wait state between a 128-bit store and the next write to its data
+  // registers, and lanes 16..31 and 48..63 of a store now and then carried the low words of
+  // the following value (64-bit stores, the FP32 form above, need no wait state).
+  static __device__ __forceinline__ void stc_if(rsrc_t r, bool ok, uint32_t i, uint32_t so, cx<double> v) {
+    __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, v), r, ok ? i * 16u + so : 0xfffffff0u, 0, 0);
   }
 };
 

@@ -7,6 +7,7 @@
 
 #include "fft_lds.hpp"
 #include "gmem.hpp"
+#include "pair_fft.hpp"
 
 namespace psatd {
 
@@ -14,7 +15,9 @@ using i64 = long long;
 
 // Intermediate layouts of the half spectrum (box of NX x NY x NZ cells, NXH = NX/2 + 1):
 //   layout A  [field][z][kx][y]   (y fastest)  -- after the x pass
-//   layout B  [field][kx][ky][z]  (z fastest)  -- after the y pass, k-space push in place
+//   layout B  [kx][ky][field][z]  (z fastest)  -- after the y pass, k-space push in place
+// In layout B the lines that one k-space column needs (11 fields, 12 with the split
+// fields of the PML) are one contiguous block.  Layout A may hold a slab of z planes only.
 // Every pass reads whole contiguous lines on one side and writes tiles of
 // consecutive lines (a short contiguous run per position) on the other.
 
@@ -29,9 +32,10 @@ template <typename T>
 struct XFwdParams {
   const T* src[11];
   uint32_t src_bytes;    // bytes of each source array
-  cx<T>* dst;            // layout A; field f starts at dst + f * npts
-  i64 npts;
-  uint32_t dst_bytes;    // bytes of one field of A
+  cx<T>* dst;            // layout A of the slab; field f starts at dst + f * fsA
+  i64 fsA;               // nzs * NXH * NY
+  uint32_t dst_bytes;    // bytes of one field of the slab
+  int zfirst, nzs;       // z planes of this launch: [zfirst, zfirst + nzs)
   int NX, NY, NZ, NXH;
   int ty;                // real y-lines per tile (even)
   int ytiles, ntiles;    // tiles per (field, z) and in total
@@ -40,22 +44,24 @@ struct XFwdParams {
                          // G1 offset of every real row) placed after the tile's lines
   int GX, GY, GZ;
   int x0, y0, z0;        // (origin - nguard) mod G, non-negative
-  FastDiv fd_ytiles, fd_NZ, fd_NX, fd_GX, fd_GY, fd_GZ, fd_nc;
+  FastDiv fd_ytiles, fd_nzs, fd_NX, fd_GX, fd_GY, fd_GZ, fd_nc;
   int ld_drow, ld_dcol;  // block stride over (complex line, x) = divmod(threads, NX)
   int wr_drow, wr_dcol;  // block stride over (kx, complex line) = divmod(threads, ty / 2)
-  int ra, rb;            // two-stage kernel with compile-time radices (ty = 2 kXTwoStageLines), or 0, 0
+  int pnl, pnl_sh, pthreads;  // pair kernels: complex lines per tile (a power of two), its shift, block size
+  PairFFT<T> pair;
   LineFFT<T> fft;
 };
 
 // P2 / P4: transform along the middle index of a tile of lines and transpose.
 // Element p of line u of field f at outer index o is at
-//   in + f*fs_in + o*os_in + u*ls_in + p*ps_in   (elements).
+//   in + f*fs_in + o*(ob_in + os_in) + u*ls_in + p*ps_in   (elements),
+// f*fs_in + o*ob_in in 64 bits (the base of a buffer resource of in_bytes), the rest in 32.
 template <typename T>
 struct YPassParams {
   const cx<T>* in;
   cx<T>* out;
-  i64 fs_in, fs_out;
-  uint32_t in_bytes, out_bytes;  // bytes of one field
+  i64 fs_in, fs_out, ob_in, ob_out;
+  uint32_t in_bytes, out_bytes;
   int os_in, ls_in, ps_in;
   int os_out, ls_out, ps_out;
   int n;                 // line length
@@ -63,8 +69,8 @@ struct YPassParams {
   int u_lo, u_hi;        // lines processed: [u_lo, u_hi)
   int utiles, nouter, ntiles;
   int p_lo, p_hi;        // output positions written: [p_lo, p_hi)
-  int ra, rb;            // two-stage kernel with compile-time radices (ra, rb) and
-                         // kYTwoStageLines lines per tile, or 0, 0
+  int pnl, pnl_sh, pthreads;  // pair kernels: lines per tile (a power of two), its shift, block size
+  PairFFT<T> pair;
   FastDiv fd_utiles, fd_nouter, fd_n, fd_nl, fd_nl_last, fd_np;
   LineFFT<T> fft;
 };
@@ -72,9 +78,9 @@ struct YPassParams {
 // P3: z-axis forward transform of 11 fields, k-space push, inverse z transform of E, B.
 template <typename T>
 struct ZPushParams {
-  cx<T>* b;              // layout B, 11 fields of npts each
+  cx<T>* b;              // layout B, 11 fields (PML: 12)
   i64 npts;              // NXH * NY * NZ
-  uint32_t field_bytes;  // bytes of one field
+  i64 fsB, csB;          // elements between the fields of a column, and between columns
   const T* coef;         // C, S1, X1, X2, X3 each npts, pre-scaled by 1/(NX NY NZ)
   uint32_t coef_bytes;   // bytes of one table
   const T* kx;           // NXH
@@ -92,12 +98,12 @@ struct ZPushParams {
   int zgroup;            // lines per transform call (the lines of a tile are transformed in groups)
   int ntiles;            // ceil(NXH * NY / ncol)
   int z_lo, z_hi;        // output z written: [z_lo, z_hi)
-  int ra, rb;            // two-stage kernel with compile-time radices (ra, rb), or 0, 0
+  int pnl, pthreads;     // pair kernels: columns per tile, block size
+  PairFFT<T> pair;
   T c2;                  // c^2
   T inv_eps0;            // 1 / eps0
   // Two-step PML (split fields): 0 = ordinary push; 1 = write the increments of the
-  // twelve split parts over the step (set A to fields 0..5, set B to 6..11 of b, which
-  // then holds 12 fields); dt and 1/(NX NY NZ) for the terms without a table.
+  // twelve split parts over the step (set A to fields 0..5, set B to 6..11 of b); dt and 1/(NX NY NZ) for the terms without a table.
   int pml;
   T dt, inv_n;
   FastDiv fd_NY, fd_NZ, fd_ncol;
@@ -108,53 +114,50 @@ struct ZPushParams {
 // arrays or scattered into the interior of G1.
 template <typename T>
 struct XInvParams {
-  const cx<T>* src;      // layout A
-  i64 npts;
-  uint32_t src_bytes;    // bytes of one field of A
+  const cx<T>* src;      // layout A of the slab
+  i64 npts;              // elements of one field of the slab
+  uint32_t src_bytes;    // bytes of one field of the slab
+  int zfirst, nzs;       // z planes of this launch: [zfirst, zfirst + nzs)
   T* dst[6];
   uint32_t dst_bytes;    // bytes of each destination array
   int NX, NY, NZ, NXH;
   int ty;                // real y-lines per tile (even)
   int y_lo, y_hi;        // y-lines processed
-  int z_lo, z_hi;        // z-planes processed
   int ytiles, ntiles;
   int scatter;           // 0: dst is box shaped; 1: dst is G1, interior only
   int GX, GY, GZ;
   int ox, oy, oz;        // origin of the interior in G1
   int gx, gy, gz;        // guard widths
   int nx;                // interior cells along x
-  FastDiv fd_ytiles, fd_nz, fd_nc, fd_NX, fd_GX, fd_GY, fd_GZ;
+  FastDiv fd_ytiles, fd_nz, fd_nc, fd_NX, fd_nx, fd_GX, fd_GY, fd_GZ;  // fd_nz: nzs; fd_nx: columns written
   int nthreads;          // block size the tile was fitted for (kXInvThreads, or kLineThreads
                          // when a line's butterflies exceed the smaller block)
-  int ra, rb;            // two-stage kernel with compile-time radices (ty = 2 kXTwoStageLines), or 0, 0
+  int pnl, pnl_sh, pthreads;  // pair kernels: complex lines per tile (a power of two), its shift, block size
+  PairFFT<T> pair;
   LineFFT<T> fft;
 };
 
-// Line schedules (RA, RB), N = RA * RB, with a compiled two-stage z kernel
-// (single-column tiles of 256 threads, every offset a compile-time constant).
-constexpr int kZTwoStage[][2] = {{16, 20}, {20, 16}, {16, 16}, {24, 24}, {32, 17}, {17, 32}};
-constexpr int kZTwoStageThreads = 256;
-// LDS slots per line of the two-stage kernel: the intermediate rows of RB
-// butterflies padded to RA | 1 slots, or the N points in natural order.
-constexpr int two_stage_slots(int ra, int rb) { return ((rb * (ra | 1) > ra * rb) ? rb * (ra | 1) : ra * rb) | 1; }
-
-// Line schedules (RA, RB) with compiled two-stage y kernels, their lines per tile,
-// LDS slots per line (RB padded rows of RA | 1 slots) and block size (one
-// butterfly per thread in either stage).
-constexpr int kYTwoStage[][2] = {{16, 20}, {20, 16}, {16, 16}, {24, 24}, {32, 17}, {17, 32}};
-constexpr int kYTwoStageLines = 16;
-constexpr int two_stage_y_slots(int ra, int rb) { return (rb * (ra | 1)) | 1; }
-constexpr int two_stage_y_threads(int ra, int rb) {
-  return ((kYTwoStageLines * (ra > rb ? ra : rb) + 63) / 64) * 64;
+// Pair kernels: slots per line of `lines` lines, LDS of a block's lines and stage B twiddles, and
+// the largest block of a class (FP64, large radices: a SIMD's registers for one wavefront; the
+// z pass, with eleven lines per block, takes the larger block and half the registers).
+// Where the lanes of an access walk across the lines first (lines > 0: a power of two), one
+// cycle serves g of them (16 FP32 values; 8 FP32 pairs or FP64 values): fewer lines than g
+// have to lie g / lines slots apart (mod g), more an odd number of 16 bytes.  Lines that are
+// walked one after the other (lines = 0) follow on at the column pitch.
+constexpr int pair_line(int ra, int pitch, int lines, bool fp64) {
+  const int g = fp64 ? 8 : 16;
+  int ld = ra * pitch;
+  if (lines == 0) return ld;
+  if (lines < g)
+    while (ld % g != g / lines % g) ++ld;
+  else
+    while (fp64 ? ld % 2 != 1 : ld % 4 != 2) ++ld;
+  return ld;
 }
-
-// Line schedules (RA, RB) with compiled two-stage x kernels (single boxes), complex
-// lines (pairs of real rows) per tile, and block size (one butterfly per thread).
-constexpr int kXTwoStage[][2] = {{24, 24}, {32, 18}, {18, 32}, {16, 20}, {20, 16}, {16, 16}, {32, 17}, {17, 32}};
-constexpr int kXTwoStageLines = 8;
-constexpr int two_stage_x_threads(int ra, int rb) {
-  return ((kXTwoStageLines * (ra > rb ? ra : rb) + 63) / 64) * 64;
+constexpr size_t pair_lds_bytes(int ra, int rb, int ld, int lines, size_t csize) {
+  return ((size_t)lines * ld + ((size_t)lines * ld & 1)) * csize + (size_t)ra * pair_tw_pitch(rb) * 16;
 }
+constexpr int pair_threads_max(bool fp64, int cls, bool z) { return fp64 && cls % 2 == 1 && !z ? 256 : 512; }
 
 // Threads per block of the x and y passes.
 constexpr int kLineThreads = 512;
@@ -207,16 +210,34 @@ template <typename T>
 void launch_ypass(const YPassParams<T>& p, int inverse, hipStream_t s);
 template <typename T>
 void launch_zpush(const ZPushParams<T>& p, int nthreads, hipStream_t s);
-// The two-stage z kernel for p.ra, p.rb (one of kZTwoStage).
-template <typename T>
-void launch_zpush_two_stage(const ZPushParams<T>& p, hipStream_t s);
 template <typename T>
 void launch_xinv(const XInvParams<T>& p, hipStream_t s);
 
+// The pair kernels (class C of p.pair's radices; batches hold classes 0 and 2 only).
+template <typename T, int C>
+void launch_pair_xfwd_c(const XFwdParams<T>& p, hipStream_t s);
+template <typename T, int C>
+void launch_pair_ypass_c(const YPassParams<T>& p, int inverse, hipStream_t s);
+template <typename T, int C>
+void launch_pair_zpush_c(const ZPushParams<T>& p, hipStream_t s);
+template <typename T, int C>
+void launch_pair_xinv_c(const XInvParams<T>& p, hipStream_t s);
+template <typename T, int C>
+void launch_pair_xfwd_batch(const BatchArgs<XFwdParams<T>>& a, int threads, size_t lds, hipStream_t s);
+template <typename T, int C>
+void launch_pair_ypass_batch(const BatchArgs<YPassParams<T>>& a, int inverse, int threads, size_t lds, hipStream_t s);
+template <typename T, int C>
+void launch_pair_zpush_batch(const BatchArgs<ZPushParams<T>>& a, int threads, size_t lds, hipStream_t s);
+template <typename T, int C>
+void launch_pair_xinv_batch(const BatchArgs<XInvParams<T>>& a, int threads, size_t lds, hipStream_t s);
+
 // Tables (FP64 math, stored at working precision).
+// Stage B twiddles of a radix pair (see PairFFT::tw), ra * pair_tw_pitch(rb) entries.
+void launch_pair_twiddles(void* dst, int ra, int rb, int fp64, hipStream_t s);
 // Stage-major twiddle table of `sch` (see fft_lds.hpp), n entries allocated.
 void launch_twiddles(void* dst, const LineSchedule& sch, int fp64, hipStream_t s);
-void launch_bluestein(void* chirp, void* filt, int n, int m, int fp64, hipStream_t s);
+// Chirp (`count` entries, zero from n on) and filter (m entries) of a chirp-z line.
+void launch_bluestein(void* chirp, int count, void* filt, int n, int m, int fp64, hipStream_t s);
 void launch_modk(double* dst, int n, int count, double d, int order, int staggered, hipStream_t s);
 // kappa = k_s exp(i k d / 2) of each DFT index at working precision (staggered grids).
 void launch_shifted(const double* ks, void* dst, int n, int count, int fp64, hipStream_t s);

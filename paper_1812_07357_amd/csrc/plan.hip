@@ -217,6 +217,108 @@ bool make_axis(int n, int emax, Axis* a) {
   return true;
 }
 
+// ---------------------------------------------------------------- radix pairs
+// An axis whose length has a pair (see pair_fft.hpp) runs on the pair kernels: one LDS
+// exchange per transform instead of one per Stockham stage.  A 17-smooth length takes a
+// direct pair; any other length the chirp-z form over the cheapest pair product
+// m >= 2n - 1.  Lengths without either (smooth ones such as 245 = 5 * 7 * 7 whose factors
+// do not group into two compiled radices, and long ones) stay on the Stockham kernels.
+struct PairAxis {
+  int n = 0, m = 0, ra = 0, rb = 0, blue = 0, cls = 0;  // ra = 0: no pair
+  double cost = 0.0;
+  void* tw = nullptr;
+  void* chirp = nullptr;
+  void* filt = nullptr;
+};
+
+// Modelled VALU instructions per element of one pair stage (the Stockham stage costs above
+// for the shared radices, the others from the same operation counts).
+double pair_stage_cost(int r) {
+  switch (r) {
+    case 1: return 4.0;
+    case 14: return 37.0;
+    case 15: return 38.0;
+    case 21: return 45.0;
+    case 22: return 51.0;
+    case 25: return 42.0;
+    case 26: return 55.0;
+    case 27: return 46.0;
+    case 28: return 43.0;
+    case 30: return 45.0;
+    case 33: return 57.0;
+    case 34: return 63.0;
+    default: return radix_cost(r);
+  }
+}
+
+template <int C>
+void collect_pairs(int n, std::vector<PairAxis>& out) {
+  // the larger radices leave fewer wavefronts per SIMD; an uneven pair leaves most threads
+  // idle in stage A, which has rb butterflies per line where stage B has ra (a z line of 24
+  // points as one 24-point butterfly took 3 times as long as 6 * 4)
+  const double weight = C % 2 == 0 ? 1.0 : 1.2;
+  for (int ra = 1; ra <= 36; ++ra)
+    for (int rb = 1; rb <= ra; ++rb) {
+      if (!in_list(ra, typename radices<C>::a{}) || !in_list(rb, typename radices<C>::b{})) continue;
+      PairAxis a;
+      a.n = n;
+      a.m = ra * rb;
+      a.ra = ra;
+      a.rb = rb;
+      a.cls = C;
+      a.blue = chirp_class(C);
+      if (a.blue ? a.m < 2 * n - 1 : a.m != n) continue;
+      a.cost = weight * a.m * (pair_stage_cost(ra) + pair_stage_cost(rb)) * (1.0 + 0.1 * ((double)ra / rb - 1.0));
+      out.push_back(a);
+    }
+}
+
+// Whether every prime factor of n has a compiled DFT (at most 17).
+bool smooth_length(int n) {
+  for (int q : {2, 3, 5, 7, 11, 13, 17})
+    while (n % q == 0) n /= q;
+  return n == 1;
+}
+
+// Pairs of length n, cheapest first; `large`: the classes of large radices too.
+std::vector<PairAxis> ranked_pairs(int n, bool large) {
+  std::vector<PairAxis> out;
+  if (smooth_length(n)) {
+    collect_pairs<0>(n, out);
+    if (large) collect_pairs<1>(n, out);
+  } else {
+    collect_pairs<2>(n, out);
+    if (large) collect_pairs<3>(n, out);
+  }
+  std::stable_sort(out.begin(), out.end(), [](const PairAxis& x, const PairAxis& y) { return x.cost < y.cost; });
+  return out;
+}
+
+// LDS slots per line of a pair on an axis with `nl` lines per tile (see pair_line).
+int pair_slots(const PairAxis& a, int axis, int nl, bool fp64) {
+  const int pitch = fp64 ? pair_pitch<double>(a.rb) : pair_pitch<float>(a.rb);
+  return pair_line(a.ra, pitch, axis == 2 ? 0 : nl, fp64);
+}
+
+template <typename T>
+PairFFT<T> pair_fft(const PairAxis& a, int axis, int nl) {
+  PairFFT<T> P{};
+  P.n = a.n;
+  P.m = a.m;
+  P.ra = a.ra;
+  P.rb = a.rb;
+  P.pb = pair_pitch<T>(a.rb);
+  P.ld = pair_slots(a, axis, nl, sizeof(T) == 8);
+  P.fa = make_fastdiv((uint32_t)std::max(1, a.ra));
+  P.fb = make_fastdiv((uint32_t)std::max(1, a.rb));
+  P.tw = (const Tw<T>*)a.tw;
+  P.chirp = (const Tw<T>*)a.chirp;
+  P.filt = (const Tw<T>*)a.filt;
+  return P;
+}
+
+int pair_block(int lines, int ra) { return (lines * ra + 63) / 64 * 64; }
+
 template <typename T>
 LineFFT<T> line_fft(const Axis& a) {
   LineFFT<T> L{};
@@ -253,11 +355,6 @@ size_t csz() {
 
 }  // namespace
 
-namespace {
-// Default set of passes on two-stage kernels (bit i = P(i+1)): all but the x inverse.
-constexpr int kTwoStageDefault = 1 | 2 | 4 | 8;
-}  // namespace
-
 struct psatd_plan {
   psatd_plan_desc d{};
   int NX = 0, NY = 0, NZ = 0, NXH = 0;
@@ -272,10 +369,12 @@ struct psatd_plan {
   int nl_y = 0;      // lines per P2/P4 tile
   int zthreads = 0;  // threads of the P3 block
   int zcols = 0;     // (kx, ky) columns per P3 tile
-  // Passes (bit i = P(i+1)) that run the compiled two-stage kernel when their
-  // schedule has one; the autotuner keeps a pass's bit only if that kernel is the
-  // faster of the two.  The x inverse starts on the run-time-schedule kernel.
-  int two_stage_mask = kTwoStageDefault;
+  // Radix pairs of the axes (ra = 0: the axis runs on the Stockham kernels) and their tiles:
+  // complex x lines, y lines, (kx, ky) columns.
+  PairAxis pair[3];
+  int pair_nl[3] = {0, 0, 0};
+  bool large_radices = true;
+  bool interleaved = true;  // layout B [kx][ky][field][z]; false: [field][kx][ky][z] (see build_plan)
   double* kd = nullptr;  // FP64 modified k: kx (NXH), ky (NY), kz (NZ)
   void* kw = nullptr;    // same at working precision
   void* kwc = nullptr;   // staggered grids: kappa = k_s exp(i k d / 2) per axis index, complex
@@ -391,6 +490,50 @@ void choose_z_tile(psatd_plan* p, const LineSchedule& szs, int em, size_t cs) {
       }
 }
 
+// Pair tiles, a power of two lines in x and y so that lanes split into (line, position) by a
+// shift.  x: the lines whose two rows each give 128 contiguous bytes on the transposed
+// side, more for short lines (at least a wavefront per block); y: the lines of 128 contiguous
+// bytes, more for short lines (about 4608 points in FP32, 2304 in FP64).  x tiles of as many
+// points ran slower: 288-point lines 205 us at 16 lines per tile, 174 us at 8 (box 288x160x160).
+// z: the columns of about 320 points, fewer where the block or (several columns) 80 KB of LDS
+// is exceeded.  0: the pair does not fit this device.
+int pair_tile(const PairAxis& a, int axis, bool fp64, int fields) {
+  const size_t cs = fp64 ? 16 : 8;
+  const int tmax = pair_threads_max(fp64, a.cls, axis == 2);
+  if (axis == 2) {
+    for (int c = std::max(1, std::min(16, 320 / a.n)); c >= 1; --c)
+      if (fields * c * a.ra <= tmax &&
+          pair_lds_bytes(a.ra, a.rb, pair_slots(a, 2, 0, fp64), fields * c, cs) <= (c > 1 ? std::min<size_t>(80 * 1024, lds_limit()) : lds_limit()))
+        return c;
+    return 0;
+  }
+  const int points = fp64 ? 2304 : 4608, least = 128 / (int)(axis == 0 ? 2 * cs : cs);
+  const size_t cap = std::min<size_t>(80 * 1024, lds_limit());
+  auto fits = [&](int nl) {
+    return nl * a.ra <= tmax &&
+           pair_lds_bytes(a.ra, a.rb, pair_slots(a, axis, nl, fp64), nl, cs) + (axis == 0 ? (size_t)a.n * sizeof(int) : 0) <= cap;
+  };
+  auto larger = [&](int nl) { return axis == 0 ? nl * a.ra > 64 : nl * a.m > points; };
+  int nl = 64;
+  while (nl > 1 && (!fits(nl) || (nl > least && larger(nl)))) nl /= 2;
+  return fits(nl) ? nl : 0;
+}
+
+// The tile parameter psatd_plan_schedule reports for an axis on the pair kernels.
+int pair_report_tile(const psatd_plan* p, int axis) {
+  return axis == 0 ? 2 * p->pair_nl[0] : axis == 1 ? p->pair_nl[1] : pair_block(11 * p->pair_nl[2], p->pair[2].ra);
+}
+
+// Takes pair `a` for an axis if it fits (tile and LDS).
+bool take_pair(psatd_plan* p, int axis, const PairAxis& a) {
+  const int nl = pair_tile(a, axis, p->fp64 != 0, 11);
+  if (nl < 1) return false;
+  p->pair[axis] = a;
+  p->pair_nl[axis] = nl;
+  if (axis == 2) p->zcols = nl;
+  return true;
+}
+
 // ---------------------------------------------------------------- static scratch
 // psatd_step_g1_noalloc runs the same five passes with their two spectral
 // workspaces in a fixed device array instead of the plan's own, so a step
@@ -440,7 +583,12 @@ int scratch_slot(ScratchSlot** out) {
   return PSATD_OK;
 }
 
-int build_plan(const psatd_plan_desc* d, psatd_plan** out) {
+// Layout B strides of plan p for `fields` fields: between the fields of a column, between columns.
+i64 b_field_stride(const psatd_plan* p) { return p->interleaved ? (i64)p->NZ : (i64)p->npts; }
+i64 b_column_stride(const psatd_plan* p, int fields) { return p->interleaved ? (i64)fields * p->NZ : (i64)p->NZ; }
+
+// large: pair classes of large radices (batches run the small ones only).
+int build_plan(const psatd_plan_desc* d, psatd_plan** out, bool large = true) {
   int rc = validate(d);
   if (rc) return rc;
   psatd_plan* p = new psatd_plan;
@@ -451,6 +599,7 @@ int build_plan(const psatd_plan_desc* d, psatd_plan** out) {
   p->NXH = p->NX / 2 + 1;
   p->npts = (long long)p->NXH * p->NY * p->NZ;
   p->ncell = (long long)p->NX * p->NY * p->NZ;
+  p->large_radices = large;
   p->fp64 = d->precision == PSATD_FP64;
   p->rsize = p->fp64 ? 8 : 4;
   const int em = p->fp64 ? emax<double>::v : emax<float>::v;
@@ -480,6 +629,17 @@ int build_plan(const psatd_plan_desc* d, psatd_plan** out) {
     return fail(PSATD_EUNSUPPORTED, "box %dx%dx%d does not fit the LDS / register tiling of this build", p->NX,
                 p->NY, p->NZ);
   }
+  // One kx plane of layout B is addressed through 32-bit offsets; a plane of 4 GiB or more
+  // (a thin box) keeps its fields apart, and its z pass stays on the Stockham kernel.
+  p->interleaved = (double)p->NY * 12.0 * p->NZ * (double)cs < 4294967296.0;
+  {
+    const int n[3] = {p->NX, p->NY, p->NZ};
+    for (int a = 0; a < 3; ++a) {
+      if (a == 2 && !p->interleaved) continue;
+      for (const PairAxis& c : ranked_pairs(n[a], large))
+        if (take_pair(p, a, c)) break;
+    }
+  }
   // Every array is addressed through 32-bit byte offsets.
   const double field_bytes = (double)p->npts * cs;
   if (field_bytes >= 4294967296.0 || (double)p->ncell * p->rsize >= 4294967296.0) {
@@ -488,9 +648,19 @@ int build_plan(const psatd_plan_desc* d, psatd_plan** out) {
   }
   const size_t npts = (size_t)p->npts;
   const size_t tws = p->fp64 ? sizeof(Tw<double>) : sizeof(Tw<float>);
-  for (Axis* a : {&p->ax, &p->ay, &p->az}) {
-    if ((rc = dalloc(p, &a->tw, tws * a->sch.n)) ||
-        (a->blue && ((rc = dalloc(p, &a->chirp, tws * a->n)) || (rc = dalloc(p, &a->filt, tws * a->sch.n))))) {
+  Axis* const axes[3] = {&p->ax, &p->ay, &p->az};
+  for (int k = 0; k < 3; ++k) {
+    Axis* const a = axes[k];
+    PairAxis& q = p->pair[k];
+    if (q.ra) {
+      // room for the twiddles of any pair of this length (the autotuner may take another)
+      rc = dalloc(p, &q.tw, tws * 2 * q.m);
+      if (!rc && q.blue && !(rc = dalloc(p, &q.chirp, tws * q.m))) rc = dalloc(p, &q.filt, tws * q.m);
+    } else {
+      rc = dalloc(p, &a->tw, tws * a->sch.n);
+      if (!rc && a->blue && !(rc = dalloc(p, &a->chirp, tws * a->n))) rc = dalloc(p, &a->filt, tws * a->sch.n);
+    }
+    if (rc) {
       std::string msg = g_err;
       free_plan(p);
       return fail(rc, "%s", msg.c_str());
@@ -507,9 +677,16 @@ int build_plan(const psatd_plan_desc* d, psatd_plan** out) {
     return fail(rc, "%s", msg.c_str());
   }
   hipStream_t s = nullptr;
-  for (Axis* a : {&p->ax, &p->ay, &p->az}) {
-    launch_twiddles(a->tw, a->sch, p->fp64, s);
-    if (a->blue) launch_bluestein(a->chirp, a->filt, a->n, a->sch.n, p->fp64, s);
+  for (int k = 0; k < 3; ++k) {
+    const Axis* const a = axes[k];
+    const PairAxis& q = p->pair[k];
+    if (q.ra) {
+      launch_pair_twiddles(q.tw, q.ra, q.rb, p->fp64, s);
+      if (q.blue) launch_bluestein(q.chirp, q.m, q.filt, q.n, q.m, p->fp64, s);
+    } else {
+      launch_twiddles(a->tw, a->sch, p->fp64, s);
+      if (a->blue) launch_bluestein(a->chirp, a->n, a->filt, a->n, a->sch.n, p->fp64, s);
+    }
   }
   const int stag = (d->flags & PSATD_FLAG_STAGGERED) ? 1 : 0;
   launch_modk(p->kd, p->NX, p->NXH, d->dx, d->order, stag, s);
@@ -565,59 +742,9 @@ struct StepIO {
   int pml = 0;                 // two-step PML: P3 writes the twelve split increments (wsB holds 12 fields)
 };
 
-// The compiled two-stage z kernel applies when a box's z tiles hold one column,
-// its z lines are transformed directly in exactly two stages, the pair of
-// radices is one of kZTwoStage and the tile fits the LDS of one workgroup.
-void two_stage_radices(const psatd_plan* p, size_t csize, int* ra, int* rb) {
-  *ra = *rb = 0;
-  const LineSchedule& s = p->az.sch;
-  if (p->zcols != 1 || p->az.blue || s.nstages != 2) return;
-  for (const auto& pr : kZTwoStage)
-    if (pr[0] == s.radix[0] && pr[1] == s.radix[1] &&
-        (size_t)11 * two_stage_slots(pr[0], pr[1]) * csize + (size_t)pr[0] * (pr[1] - 1) * 16 <= lds_limit()) {
-      *ra = pr[0];
-      *rb = pr[1];
-      return;
-    }
-}
-
-// The compiled two-stage x kernels apply to single boxes whose x lines are transformed
-// directly in exactly two stages with radices in kXTwoStage, the tile (and P1's
-// column table) fitting in a quarter of the LDS a workgroup may use.
-void two_stage_x_radices(const psatd_plan* p, size_t csize, int* ra, int* rb) {
-  *ra = *rb = 0;
-  const LineSchedule& s = p->ax.sch;
-  if (p->ax.blue || s.nstages != 2) return;
-  for (const auto& pr : kXTwoStage)
-    if (pr[0] == s.radix[0] && pr[1] == s.radix[1] &&
-        (size_t)kXTwoStageLines * two_stage_slots(pr[0], pr[1]) * csize + (size_t)(p->NX + 3) * sizeof(int) +
-                (size_t)pr[0] * (pr[1] - 1) * 16 <=
-            lds_limit() / 3) {
-      *ra = pr[0];
-      *rb = pr[1];
-      return;
-    }
-}
-
-// The compiled two-stage y kernels apply when the y lines are transformed
-// directly in exactly two stages whose radices are one of kYTwoStage, and a tile
-// of kYTwoStageLines lines fits in LDS with room for a second block per CU.
-void two_stage_y_radices(const psatd_plan* p, size_t csize, int* ra, int* rb) {
-  *ra = *rb = 0;
-  const LineSchedule& s = p->ay.sch;
-  if (p->ay.blue || s.nstages != 2) return;
-  for (const auto& pr : kYTwoStage)
-    if (pr[0] == s.radix[0] && pr[1] == s.radix[1] &&
-        (size_t)kYTwoStageLines * two_stage_y_slots(pr[0], pr[1]) * csize + (size_t)pr[0] * (pr[1] - 1) * 16 <=
-            lds_limit() / 2) {
-      *ra = pr[0];
-      *rb = pr[1];
-      return;
-    }
-}
-
 template <typename T>
 void set_ypass(YPassParams<T>& y, int nfields) {
+  if (y.pair.ra) y.nl = y.pnl;
   y.utiles = (y.u_hi - y.u_lo + y.nl - 1) / y.nl;
   y.nl_last = (y.u_hi - y.u_lo) - (y.utiles - 1) * y.nl;
   y.ntiles = nfields * y.nouter * y.utiles;
@@ -647,13 +774,61 @@ struct StepParams {
   XInvParams<T> x5;
 };
 
+// Slabs: P1 and P2 (and P4 and P5) may run on a range of z planes at a time, layout A then
+// holding that range only.
+template <typename T>
+void set_slab(XFwdParams<T>& x, int z0, int nz) {
+  x.zfirst = z0;
+  x.nzs = nz;
+  x.fd_nzs = make_fastdiv(nz);
+  x.fsA = (i64)nz * x.NXH * x.NY;
+  x.dst_bytes = (uint32_t)(x.fsA * (i64)sizeof(cx<T>));
+  x.ntiles = 11 * nz * x.ytiles;
+}
+template <typename T>
+void set_slab(XInvParams<T>& x, int z0, int nz) {
+  x.zfirst = z0;
+  x.nzs = nz;
+  x.fd_nz = make_fastdiv(nz);
+  x.npts = (i64)nz * x.NXH * x.NY;
+  x.src_bytes = (uint32_t)(x.npts * (i64)sizeof(cx<T>));
+  x.ntiles = 6 * nz * x.ytiles;
+}
+template <typename T>
+void set_slab_fwd(YPassParams<T>& y, const psatd_plan* p, int z0, int nz) {
+  y.fs_in = (i64)nz * p->NXH * p->NY;
+  y.in_bytes = (uint32_t)(y.fs_in * (i64)sizeof(cx<T>));
+  y.out += z0;
+  y.out_bytes -= (uint32_t)(z0 * (int)sizeof(cx<T>));
+  y.u_lo = 0;
+  y.u_hi = nz;
+  set_ypass(y, 11);
+}
+template <typename T>
+void set_slab_inv(YPassParams<T>& y, const psatd_plan* p, int z0, int nz) {
+  y.fs_out = (i64)nz * p->NXH * p->NY;
+  y.out_bytes = (uint32_t)(y.fs_out * (i64)sizeof(cx<T>));
+  y.in += z0;
+  y.in_bytes -= (uint32_t)(z0 * (int)sizeof(cx<T>));
+  y.u_lo = 0;
+  y.u_hi = nz;
+  set_ypass(y, 6);
+}
+
+int log2_of(int v) {
+  int s = 0;
+  while ((1 << s) < v) ++s;
+  return s;
+}
+
 // Kernel parameters of the five passes of one step of plan p with the given inputs / outputs.
 template <typename T>
-void build_step(psatd_plan* p, const StepIO& io, StepParams<T>& sp, bool batched = false) {
+void build_step(psatd_plan* p, const StepIO& io, StepParams<T>& sp) {
   const int NX = p->NX, NY = p->NY, NZ = p->NZ, NXH = p->NXH;
   const long long npts = p->npts;
-  const uint32_t fbytes = (uint32_t)(npts * (long long)sizeof(cx<T>));
   const int nth = kLineThreads;
+  const int fields = io.pml ? 12 : 11;
+  const i64 fsB = b_field_stride(p), csB = b_column_stride(p, fields);
   cx<T>* A = (cx<T>*)io.wsA;
   cx<T>* B = (cx<T>*)io.wsB;
   const T* kw = (const T*)p->kw;
@@ -663,15 +838,11 @@ void build_step(psatd_plan* p, const StepIO& io, StepParams<T>& sp, bool batched
   for (int f = 0; f < 11; ++f) x1.src[f] = (const T*)io.src[f];
   x1.src_bytes = (uint32_t)(io.src_elems * (long long)sizeof(T));
   x1.dst = A;
-  x1.npts = npts;
-  x1.dst_bytes = fbytes;
   x1.NX = NX;
   x1.NY = NY;
   x1.NZ = NZ;
   x1.NXH = NXH;
   x1.ty = p->ty1;
-  x1.ytiles = (NY + x1.ty - 1) / x1.ty;
-  x1.ntiles = 11 * NZ * x1.ytiles;
   x1.gather = io.gather;
   x1.xtab = io.gather && p->xtab;
   x1.GX = io.GX;
@@ -680,8 +851,6 @@ void build_step(psatd_plan* p, const StepIO& io, StepParams<T>& sp, bool batched
   x1.x0 = io.x0;
   x1.y0 = io.y0;
   x1.z0 = io.z0;
-  x1.fd_ytiles = make_fastdiv(x1.ytiles);
-  x1.fd_NZ = make_fastdiv(NZ);
   x1.fd_NX = make_fastdiv(NX);
   x1.fd_nc = make_fastdiv(x1.ty / 2);
   if (io.gather) {
@@ -694,56 +863,49 @@ void build_step(psatd_plan* p, const StepIO& io, StepParams<T>& sp, bool batched
   x1.wr_drow = nth / (x1.ty / 2);
   x1.wr_dcol = nth % (x1.ty / 2);
   x1.fft = line_fft<T>(p->ax);
-  int xra = 0, xrb = 0;
-  if (!batched) two_stage_x_radices(p, sizeof(cx<T>), &xra, &xrb);
-  if (p->two_stage_mask & 1) {
-    x1.ra = xra;
-    x1.rb = xrb;
+  if (p->pair[0].ra) {
+    x1.pair = pair_fft<T>(p->pair[0], 0, p->pair_nl[0]);
+    x1.pnl = p->pair_nl[0];
+    x1.pnl_sh = log2_of(x1.pnl);
+    x1.pthreads = pair_block(x1.pnl, x1.pair.ra);
+    x1.ty = 2 * x1.pnl;
   }
-  if (x1.ra) {  // tiles of kXTwoStageLines complex lines
-    x1.ty = 2 * kXTwoStageLines;
-    x1.ytiles = (NY + x1.ty - 1) / x1.ty;
-    x1.ntiles = 11 * NZ * x1.ytiles;
-    x1.fd_ytiles = make_fastdiv(x1.ytiles);
-    x1.fd_nc = make_fastdiv(x1.ty / 2);
-  }
+  x1.ytiles = (NY + x1.ty - 1) / x1.ty;
+  x1.fd_ytiles = make_fastdiv(x1.ytiles);
+  set_slab(x1, 0, NZ);
 
   YPassParams<T>& y2 = sp.y2;
   y2 = YPassParams<T>{};
   y2.in = A;
   y2.out = B;
-  y2.fs_in = npts;
-  y2.fs_out = npts;
-  y2.in_bytes = fbytes;
-  y2.out_bytes = fbytes;
+  y2.fs_out = fsB;
   y2.os_in = NY;
   y2.ls_in = NXH * NY;
   y2.ps_in = 1;
-  y2.os_out = NY * NZ;
+  y2.ob_out = NY * csB;
   y2.ls_out = 1;
-  y2.ps_out = NZ;
+  y2.ps_out = (int)csB;
+  y2.out_bytes = (uint32_t)(((NY - 1) * csB + NZ) * (i64)sizeof(cx<T>));
   y2.n = NY;
   y2.nl = p->nl_y;
-  int yra = 0, yrb = 0;
-  if (!batched) two_stage_y_radices(p, sizeof(cx<T>), &yra, &yrb);
-  if (p->two_stage_mask & 2) {
-    y2.ra = yra;
-    y2.rb = yrb;
-  }
-  if (y2.ra) y2.nl = kYTwoStageLines;
-  y2.u_lo = 0;
-  y2.u_hi = NZ;
   y2.nouter = NXH;
   y2.p_lo = 0;
   y2.p_hi = NY;
-  set_ypass(y2, 11);
   y2.fft = line_fft<T>(p->ay);
+  if (p->pair[1].ra) {
+    y2.pair = pair_fft<T>(p->pair[1], 1, p->pair_nl[1]);
+    y2.pnl = p->pair_nl[1];
+    y2.pnl_sh = log2_of(y2.pnl);
+    y2.pthreads = pair_block(y2.pnl, y2.pair.ra);
+  }
+  set_slab_fwd(y2, p, 0, NZ);
 
   ZPushParams<T>& z3 = sp.z3;
   z3 = ZPushParams<T>{};
   z3.b = B;
   z3.npts = npts;
-  z3.field_bytes = fbytes;
+  z3.fsB = fsB;
+  z3.csB = csB;
   z3.coef = (const T*)p->coef;
   z3.coef_bytes = (uint32_t)(npts * (long long)sizeof(T));
   z3.kx = kw;
@@ -759,70 +921,60 @@ void build_step(psatd_plan* p, const StepIO& io, StepParams<T>& sp, bool batched
   z3.NY = NY;
   z3.NZ = NZ;
   z3.NXH = NXH;
-  z3.ncol = p->zcols;
-  z3.zgroup = z_group(p->az.sch, p->zthreads, emax<T>::v, sizeof(cx<T>), 11 * p->zcols);
-  z3.ntiles = (NXH * NY + p->zcols - 1) / p->zcols;
   z3.z_lo = io.z_lo;
   z3.z_hi = io.z_hi;
   z3.c2 = T(p->d.c * p->d.c);
   z3.inv_eps0 = T(1.0 / p->d.eps0);
   z3.fd_NY = make_fastdiv(NY);
   z3.fd_NZ = make_fastdiv(NZ);
-  z3.fd_ncol = make_fastdiv(p->zcols);
   z3.fft = line_fft<T>(p->az);
   z3.pml = io.pml;
   z3.dt = T(p->d.dt);
   z3.inv_n = T(1.0 / ((double)NX * NY * NZ));
-  if (io.pml) {  // twelve lines per column in LDS: fewer columns per tile if needed
-    int nc = p->zcols;
+  int nc = p->zcols;
+  if (p->pair[2].ra) {
+    // PML: twelve lines per column, maybe fewer columns (or none: the Stockham kernel)
+    const int pc = pair_tile(p->pair[2], 2, p->fp64 != 0, fields);
+    if (pc > 0) {
+      z3.pair = pair_fft<T>(p->pair[2], 2, 0);
+      z3.pnl = nc = pc;
+      z3.pthreads = pair_block(fields * pc, z3.pair.ra);
+    }
+  } else if (io.pml) {
     while (nc > 1 && (size_t)12 * nc * lds_line(p->az.sch.n) * sizeof(cx<T>) > z_lds(nc)) --nc;
-    z3.ncol = nc;
-    z3.ntiles = (NXH * NY + nc - 1) / nc;
-    z3.fd_ncol = make_fastdiv(nc);
-    z3.zgroup = z_group(p->az.sch, p->zthreads, emax<T>::v, sizeof(cx<T>), 12 * nc);
   }
-  if (!batched && (p->two_stage_mask & 4)) {
-    two_stage_radices(p, sizeof(cx<T>), &z3.ra, &z3.rb);
-    // PML: the two-stage kernel keeps a twelfth line in LDS
-    if (io.pml && z3.ra &&
-        (size_t)12 * two_stage_slots(z3.ra, z3.rb) * sizeof(cx<T>) + (size_t)z3.ra * (z3.rb - 1) * 16 > lds_limit())
-      z3.ra = z3.rb = 0;
-  }
+  z3.ncol = nc;
+  z3.ntiles = (NXH * NY + nc - 1) / nc;
+  z3.fd_ncol = make_fastdiv(nc);
+  z3.zgroup = z_group(p->az.sch, p->zthreads, emax<T>::v, sizeof(cx<T>), fields * nc);
 
   YPassParams<T>& y4 = sp.y4;
   y4 = YPassParams<T>{};
   y4.in = B;
   y4.out = A;
-  y4.fs_in = npts;
-  y4.fs_out = npts;
-  y4.in_bytes = fbytes;
-  y4.out_bytes = fbytes;
-  y4.os_in = NY * NZ;
+  y4.fs_in = fsB;
+  y4.ob_in = NY * csB;
   y4.ls_in = 1;
-  y4.ps_in = NZ;
+  y4.ps_in = (int)csB;
+  y4.in_bytes = y2.out_bytes;
   y4.os_out = NY;
   y4.ls_out = NXH * NY;
   y4.ps_out = 1;
   y4.n = NY;
   y4.nl = p->nl_y;
-  if (p->two_stage_mask & 8) {
-    y4.ra = yra;
-    y4.rb = yrb;
-  }
-  if (y4.ra) y4.nl = kYTwoStageLines;
-  y4.u_lo = io.z_lo;
-  y4.u_hi = io.z_hi;
   y4.nouter = NXH;
   y4.p_lo = io.y_lo;
   y4.p_hi = io.y_hi;
-  set_ypass(y4, 6);
   y4.fft = line_fft<T>(p->ay);
+  y4.pair = y2.pair;
+  y4.pnl = y2.pnl;
+  y4.pnl_sh = y2.pnl_sh;
+  y4.pthreads = y2.pthreads;
+  set_slab_inv(y4, p, io.z_lo, io.z_hi - io.z_lo);
 
   XInvParams<T>& x5 = sp.x5;
   x5 = XInvParams<T>{};
   x5.src = A;
-  x5.npts = npts;
-  x5.src_bytes = fbytes;
   for (int f = 0; f < 6; ++f) x5.dst[f] = (T*)io.dst[f];
   x5.dst_bytes = (uint32_t)(io.dst_elems * (long long)sizeof(T));
   x5.NX = NX;
@@ -832,10 +984,6 @@ void build_step(psatd_plan* p, const StepIO& io, StepParams<T>& sp, bool batched
   x5.ty = p->ty5;
   x5.y_lo = io.y_lo;
   x5.y_hi = io.y_hi;
-  x5.z_lo = io.z_lo;
-  x5.z_hi = io.z_hi;
-  x5.ytiles = (io.y_hi - io.y_lo + x5.ty - 1) / x5.ty;
-  x5.ntiles = 6 * (io.z_hi - io.z_lo) * x5.ytiles;
   x5.scatter = io.scatter;
   x5.GX = io.GX;
   x5.GY = io.GY;
@@ -847,10 +995,9 @@ void build_step(psatd_plan* p, const StepIO& io, StepParams<T>& sp, bool batched
   x5.gy = p->d.ngy;
   x5.gz = p->d.ngz;
   x5.nx = p->d.nx;
-  x5.fd_ytiles = make_fastdiv(x5.ytiles);
-  x5.fd_nz = make_fastdiv(io.z_hi - io.z_lo);
   x5.fd_nc = make_fastdiv(x5.ty / 2);
   x5.fd_NX = make_fastdiv(NX);
+  x5.fd_nx = make_fastdiv(io.scatter ? p->d.nx : NX);
   if (io.scatter) {
     x5.fd_GX = make_fastdiv(io.GX);
     x5.fd_GY = make_fastdiv(io.GY);
@@ -858,17 +1005,49 @@ void build_step(psatd_plan* p, const StepIO& io, StepParams<T>& sp, bool batched
   }
   x5.nthreads = p->x5threads;
   x5.fft = line_fft<T>(p->ax);
-  if (p->two_stage_mask & 16) {
-    x5.ra = xra;
-    x5.rb = xrb;
+  if (p->pair[0].ra) {
+    x5.pair = x1.pair;
+    x5.pnl = x1.pnl;
+    x5.pnl_sh = x1.pnl_sh;
+    x5.pthreads = x1.pthreads;
+    x5.ty = 2 * x5.pnl;
   }
-  if (x5.ra) {
-    x5.ty = 2 * kXTwoStageLines;
-    x5.ytiles = (io.y_hi - io.y_lo + x5.ty - 1) / x5.ty;
-    x5.ntiles = 6 * (io.z_hi - io.z_lo) * x5.ytiles;
-    x5.fd_ytiles = make_fastdiv(x5.ytiles);
-    x5.fd_nc = make_fastdiv(x5.ty / 2);
+  x5.ytiles = (io.y_hi - io.y_lo + x5.ty - 1) / x5.ty;
+  x5.fd_ytiles = make_fastdiv(x5.ytiles);
+  set_slab(x5, io.z_lo, io.z_hi - io.z_lo);
+}
+
+// Calls f(integral_constant<class>) for the pair class of an axis.
+template <typename F>
+void with_class(int cls, F&& f) {
+  switch (cls) {
+    case 0: f(std::integral_constant<int, 0>{}); break;
+    case 1: f(std::integral_constant<int, 1>{}); break;
+    case 2: f(std::integral_constant<int, 2>{}); break;
+    default: f(std::integral_constant<int, 3>{}); break;
   }
+}
+
+// Each pass on the kernels its axis runs on.
+template <typename T>
+void launch_p1(const XFwdParams<T>& p, int cls, hipStream_t s) {
+  if (!p.pair.ra) return launch_xfwd<T>(p, s);
+  with_class(cls, [&](auto c) { launch_pair_xfwd_c<T, decltype(c)::value>(p, s); });
+}
+template <typename T>
+void launch_p24(const YPassParams<T>& p, int inverse, int cls, hipStream_t s) {
+  if (!p.pair.ra) return launch_ypass<T>(p, inverse, s);
+  with_class(cls, [&](auto c) { launch_pair_ypass_c<T, decltype(c)::value>(p, inverse, s); });
+}
+template <typename T>
+void launch_p3(const ZPushParams<T>& p, int nthreads, int cls, hipStream_t s) {
+  if (!p.pair.ra) return launch_zpush<T>(p, nthreads, s);
+  with_class(cls, [&](auto c) { launch_pair_zpush_c<T, decltype(c)::value>(p, s); });
+}
+template <typename T>
+void launch_p5(const XInvParams<T>& p, int cls, hipStream_t s) {
+  if (!p.pair.ra) return launch_xinv<T>(p, s);
+  with_class(cls, [&](auto c) { launch_pair_xinv_c<T, decltype(c)::value>(p, s); });
 }
 
 template <typename T>
@@ -885,15 +1064,15 @@ int run_step(psatd_plan* p, const StepIO& io, hipStream_t s, bool allow_timing =
   StepParams<T> sp;
   build_step<T>(p, io, sp);
   mk.mark(0);
-  launch_xfwd<T>(sp.x1, s);
+  launch_p1<T>(sp.x1, p->pair[0].cls, s);
   mk.mark(1);
-  launch_ypass<T>(sp.y2, 0, s);
+  launch_p24<T>(sp.y2, 0, p->pair[1].cls, s);
   mk.mark(2);
-  launch_zpush<T>(sp.z3, p->zthreads, s);
+  launch_p3<T>(sp.z3, p->zthreads, p->pair[2].cls, s);
   mk.mark(3);
-  launch_ypass<T>(sp.y4, 1, s);
+  launch_p24<T>(sp.y4, 1, p->pair[1].cls, s);
   mk.mark(4);
-  launch_xinv<T>(sp.x5, s);
+  launch_p5<T>(sp.x5, p->pair[0].cls, s);
   mk.mark(5);
   return check_hip("step kernels");
 }
@@ -905,14 +1084,14 @@ template <typename T>
 int run_pml(psatd_plan* p, const StepIO& io, void* const* parts, hipStream_t s) {
   StepParams<T> sp;
   build_step<T>(p, io, sp);
-  launch_xfwd<T>(sp.x1, s);
-  launch_ypass<T>(sp.y2, 0, s);
-  launch_zpush<T>(sp.z3, p->zthreads, s);
+  launch_p1<T>(sp.x1, p->pair[0].cls, s);
+  launch_p24<T>(sp.y2, 0, p->pair[1].cls, s);
+  launch_p3<T>(sp.z3, p->zthreads, p->pair[2].cls, s);
   for (int set = 0; set < 2; ++set) {
     YPassParams<T> y4 = sp.y4;
-    y4.in = (const cx<T>*)io.wsB + (i64)6 * set * p->npts;
-    launch_ypass<T>(y4, 1, s);
-    launch_xinv<T>(sp.x5, s);
+    y4.in += (i64)6 * set * b_field_stride(p);
+    launch_p24<T>(y4, 1, p->pair[1].cls, s);
+    launch_p5<T>(sp.x5, p->pair[0].cls, s);
     launch_pml_update(parts + 6 * set, p->pml_inc, p->pml_damp, set + 1, p->NX, p->NY, p->NZ, p->fp64, s);
   }
   return check_hip("psatd_pml_step");
@@ -1001,7 +1180,7 @@ void set_radices(LineSchedule* s, const std::vector<int>& r) {
 struct TuneEntry {
   std::vector<int> radix;
   int tile = 0;
-  int kern = -1;  // two-stage kernel bits (psatd_plan::two_stage_mask) of the axis's passes, -1 unknown
+  int kern = -1;  // passes of the axis on the pair kernels (bit i = P(i+1)), -1 unknown
 };
 std::map<std::string, TuneEntry>& tune_cache() {
   static std::map<std::string, TuneEntry> c;
@@ -1016,7 +1195,7 @@ constexpr int kTuneSchema = 3;
 bool compiled_radix(int r) {
   for (int k : kRadix)
     if (k == r) return true;
-  return false;
+  return in_list(r, radices<0>::a{}) || in_list(r, radices<1>::a{});
 }
 
 // A radix sequence is usable for a transform of length m when its radices are all
@@ -1176,7 +1355,6 @@ float time_axis(psatd_plan* p, int ax, int reps, hipStream_t s) {
   io.z_hi = p->NZ;
   StepParams<T> sp;
   build_step<T>(p, io, sp);
-  if (ax == 0) sp.x5.src = (const cx<T>*)p->wsA;
   hipEvent_t e0, e1;
   (void)hipEventCreate(&e0);
   (void)hipEventCreate(&e1);
@@ -1185,13 +1363,13 @@ float time_axis(psatd_plan* p, int ax, int reps, hipStream_t s) {
     (void)hipEventRecord(e0, s);
     for (int r = 0; r < reps; ++r) {
       if (ax == 0) {
-        launch_xfwd<T>(sp.x1, s);
-        launch_xinv<T>(sp.x5, s);
+        launch_p1<T>(sp.x1, p->pair[0].cls, s);
+        launch_p5<T>(sp.x5, p->pair[0].cls, s);
       } else if (ax == 1) {
-        launch_ypass<T>(sp.y2, 0, s);
-        launch_ypass<T>(sp.y4, 1, s);
+        launch_p24<T>(sp.y2, 0, p->pair[1].cls, s);
+        launch_p24<T>(sp.y4, 1, p->pair[1].cls, s);
       } else {
-        launch_zpush<T>(sp.z3, p->zthreads, s);
+        launch_p3<T>(sp.z3, p->zthreads, p->pair[2].cls, s);
       }
     }
     (void)hipEventRecord(e1, s);
@@ -1205,61 +1383,55 @@ float time_axis(psatd_plan* p, int ax, int reps, hipStream_t s) {
   return best;
 }
 
-// Mean milliseconds of `reps` launches of pass `pass` (0..4 = P1..P5) on scratch data.
+// Axis `a` on the pair kernels: the cheapest few pairs of the same transform length as the
+// default are timed and the fastest is kept (a cached one is reused).
 template <typename T>
-float time_pass(psatd_plan* p, int pass, int reps, hipStream_t s) {
-  StepIO io{};
-  io.wsA = p->wsA;
-  io.wsB = p->wsB;
-  T* scratch = (T*)p->wsB;
-  for (int f = 0; f < 11; ++f) io.src[f] = scratch;
-  for (int f = 0; f < 6; ++f) io.dst[f] = scratch;
-  io.src_elems = io.dst_elems = p->ncell;
-  io.y_lo = 0;
-  io.y_hi = p->NY;
-  io.z_lo = 0;
-  io.z_hi = p->NZ;
-  StepParams<T> sp;
-  build_step<T>(p, io, sp);
-  if (pass == 4) sp.x5.src = (const cx<T>*)p->wsA;
-  hipEvent_t e0, e1;
-  (void)hipEventCreate(&e0);
-  (void)hipEventCreate(&e1);
-  float best = 1e30f;
-  for (int rep = 0; rep < 2; ++rep) {  // first round warms up
-    (void)hipEventRecord(e0, s);
-    for (int r = 0; r < reps; ++r) {
-      switch (pass) {
-        case 0: launch_xfwd<T>(sp.x1, s); break;
-        case 1: launch_ypass<T>(sp.y2, 0, s); break;
-        case 2: launch_zpush<T>(sp.z3, p->zthreads, s); break;
-        case 3: launch_ypass<T>(sp.y4, 1, s); break;
-        default: launch_xinv<T>(sp.x5, s); break;
+void tune_pair(psatd_plan* p, int a, hipStream_t s) {
+  const PairAxis base = p->pair[a];
+  const int lens[3] = {p->NX, p->NY, p->NZ};
+  char key[160];
+  std::snprintf(key, sizeof key, "%s|%c|n=%d|m=%d|other=%dx%d", p->fp64 ? "fp64" : "fp32", "xyz"[a], base.n, base.m,
+                lens[(a + 1) % 3], lens[(a + 2) % 3]);
+  std::vector<PairAxis> cands;
+  for (const PairAxis& c : ranked_pairs(base.n, p->large_radices))
+    if (c.m == base.m && pair_tile(c, a, p->fp64 != 0, 11) > 0) cands.push_back(c);
+  auto use = [&](PairAxis c) {
+    c.tw = base.tw;
+    c.chirp = base.chirp;
+    c.filt = base.filt;
+    (void)take_pair(p, a, c);
+    launch_pair_twiddles(c.tw, c.ra, c.rb, p->fp64, s);
+  };
+  const auto hit = tune_cache().find(key);
+  if (hit != tune_cache().end()) {
+    const std::vector<int>& r = hit->second.radix;
+    for (const PairAxis& c : cands)
+      if (!r.empty() && c.ra == r[0] && c.rb == (r.size() > 1 ? r[1] : 1) && r.size() <= 2) {
+        use(c);
+        return;
+      }
+  }
+  if (cands.size() > 4) cands.resize(4);
+  PairAxis best = base;
+  if (cands.size() > 1) {
+    float best_ms = 1e30f;
+    for (const PairAxis& c : cands) {
+      use(c);
+      const float ms = time_axis<T>(p, a, 3, s);
+      if (hipGetLastError() != hipSuccess) continue;
+      if (ms < best_ms) {
+        best_ms = ms;
+        best = c;
       }
     }
-    (void)hipEventRecord(e1, s);
-    (void)hipEventSynchronize(e1);
-    float ms = 0.f;
-    (void)hipEventElapsedTime(&ms, e0, e1);
-    best = std::min(best, ms / reps);
+    use(best);
   }
-  (void)hipEventDestroy(e0);
-  (void)hipEventDestroy(e1);
-  return best;
-}
-
-// Whether pass `pass` has a two-stage kernel under the plan's current schedules.
-template <typename T>
-bool has_two_stage(psatd_plan* p, int pass) {
-  int ra = 0, rb = 0;
-  const size_t cs = sizeof(cx<T>);
-  if (pass == 0 || pass == 4)
-    two_stage_x_radices(p, cs, &ra, &rb);
-  else if (pass == 1 || pass == 3)
-    two_stage_y_radices(p, cs, &ra, &rb);
-  else
-    two_stage_radices(p, cs, &ra, &rb);
-  return ra > 0;
+  TuneEntry e;
+  e.radix.push_back(best.ra);
+  if (best.rb > 1) e.radix.push_back(best.rb);
+  e.tile = pair_report_tile(p, a);
+  e.kern = a == 0 ? (1 | 16) : a == 1 ? (2 | 8) : 4;
+  tune_cache()[key] = e;
 }
 
 template <typename T>
@@ -1272,6 +1444,10 @@ int autotune_plan(psatd_plan* p, hipStream_t s) {
   Axis* axes[3] = {&p->ax, &p->ay, &p->az};
   for (int a = 0; a < 3; ++a) {
     Axis& A = *axes[a];
+    if (p->pair[a].ra) {
+      tune_pair<T>(p, a, s);
+      continue;
+    }
     char key[160];
     std::snprintf(key, sizeof key, "%s|%c|n=%d|m=%d|other=%dx%d", p->fp64 ? "fp64" : "fp32", "xyz"[a], A.n,
                   A.sch.n, lens[(a + 1) % 3], lens[(a + 2) % 3]);
@@ -1353,33 +1529,6 @@ int autotune_plan(psatd_plan* p, hipStream_t s) {
       p->nl_y = best_e.tile;
     } else {
       p->zthreads = best_e.tile;
-    }
-    // Per pass of this axis, the two-stage kernel or the run-time-schedule one,
-    // whichever is faster on the chosen schedule (a cached choice is reused).
-    {
-      const int passes_of_axis[3][2] = {{0, 4}, {1, 3}, {2, -1}};
-      for (int pass : passes_of_axis[a]) {
-        if (pass < 0) continue;
-        const int bit = 1 << pass;
-        if (!has_two_stage<T>(p, pass)) continue;
-        if (hit != tune_cache().end() && hit->second.kern >= 0) {
-          p->two_stage_mask = (p->two_stage_mask & ~bit) | (hit->second.kern & bit);
-          continue;
-        }
-        // alternate the two kernels and keep each one's best time; leave the default
-        // kernel of the pass only for a gain above 2 % (run-to-run noise is about 1 %)
-        float t2 = 1e30f, t1 = 1e30f;
-        for (int rep = 0; rep < 2; ++rep) {
-          p->two_stage_mask |= bit;
-          t2 = std::min(t2, time_pass<T>(p, pass, 3, s));
-          p->two_stage_mask &= ~bit;
-          t1 = std::min(t1, time_pass<T>(p, pass, 3, s));
-        }
-        if (hipGetLastError() != hipSuccess) continue;
-        const bool two_stage_default = (kTwoStageDefault & bit) != 0;
-        if (two_stage_default ? !(t1 < 0.98f * t2) : (t2 < 0.98f * t1)) p->two_stage_mask |= bit;
-      }
-      best_e.kern = p->two_stage_mask & ((a == 0) ? (1 | 16) : (a == 1) ? (2 | 8) : 4);
     }
     tune_cache()[key] = best_e;
   }
@@ -1474,6 +1623,7 @@ struct psatd_batch {
     int total = 0;            // tiles
     int threads = 0;
     size_t lds = 0;
+    int pair = -1;            // pair class, -1: the Stockham kernels
   };
   std::vector<Class> cls[5];
   hipEvent_t done = nullptr;  // completion of the last step / replay (see psatd_plan::done)
@@ -1529,23 +1679,26 @@ size_t lds_bucket(size_t bytes) {
 
 template <typename P>
 void order_pass(const std::vector<P>& in, const std::vector<int>& nt, const std::vector<int>& thr,
-                const std::vector<size_t>& lds, std::vector<P>& out, std::vector<int>& starts,
-                std::vector<psatd_batch::Class>& cls) {
+                const std::vector<size_t>& lds, const std::vector<int>& cls_of, std::vector<P>& out,
+                std::vector<int>& starts, std::vector<psatd_batch::Class>& cls) {
+  auto pair = [&](int i) { return in[i].pair.ra > 0 ? cls_of[i] : -1; };
   const int n = (int)in.size();
   std::vector<int> idx(n);
   for (int i = 0; i < n; ++i) idx[i] = i;
   std::stable_sort(idx.begin(), idx.end(), [&](int a, int c) {
+    if (pair(a) != pair(c)) return pair(a) < pair(c);
     return thr[a] != thr[c] ? thr[a] < thr[c] : lds_bucket(lds[a]) < lds_bucket(lds[c]);
   });
   out.clear();
   cls.clear();
   for (int j = 0; j < n; ++j) {
     const int i = idx[j];
-    if (cls.empty() || cls.back().threads != thr[i] || lds_bucket(cls.back().lds) != lds_bucket(lds[i])) {
+    if (cls.empty() || cls.back().pair != pair(i) || cls.back().threads != thr[i] || lds_bucket(cls.back().lds) != lds_bucket(lds[i])) {
       psatd_batch::Class c;
       c.first = j;
       c.soff = (int)starts.size();
       c.threads = thr[i];
+      c.pair = pair(i);
       starts.push_back(0);
       cls.push_back(c);
     }
@@ -1565,38 +1718,50 @@ int bind_batch(psatd_batch* b, void* const* g1) {
   std::vector<YPassParams<T>> y2(n), y4(n), y2o, y4o;
   std::vector<ZPushParams<T>> z3(n), z3o;
   std::vector<XInvParams<T>> x5(n), x5o;
-  std::vector<int> nt[5], thr[5];
+  std::vector<int> nt[5], thr[5], pc[5];
   std::vector<size_t> ls[5];
   for (int k = 0; k < 5; ++k) {
     nt[k].resize(n);
     thr[k].resize(n);
+    pc[k].resize(n);
     ls[k].resize(n);
   }
   for (int i = 0; i < n; ++i) {
     psatd_plan* p = b->plans[i];
     const StepIO io = g1_io(p, g1, b->origins[i].data(), b->gd);
     StepParams<T> sp;
-    build_step<T>(p, io, sp, true);
+    build_step<T>(p, io, sp);
     x1[i] = sp.x1;
     y2[i] = sp.y2;
     z3[i] = sp.z3;
     y4[i] = sp.y4;
     x5[i] = sp.x5;
     const int tiles[5] = {sp.x1.ntiles, sp.y2.ntiles, sp.z3.ntiles, sp.y4.ntiles, sp.x5.ntiles};
-    const int threads[5] = {kLineThreads, kLineThreads, p->zthreads, kLineThreads, p->x5threads};
-    const size_t bytes[5] = {xfwd_lds(sp.x1), ypass_lds(sp.y2), zpush_lds(sp.z3), ypass_lds(sp.y4), xinv_lds(sp.x5)};
+    // pair blocks are rounded up to a multiple of 128 threads, so that fewer classes are needed
+    auto block = [](const auto& q, int stockham) { return q.pair.ra ? (q.pthreads + 127) / 128 * 128 : stockham; };
+    const int threads[5] = {block(sp.x1, kLineThreads), block(sp.y2, kLineThreads), block(sp.z3, p->zthreads),
+                            block(sp.y4, kLineThreads), block(sp.x5, p->x5threads)};
+    auto pair_bytes = [](const auto& q, int lines, int ints) {
+      return pair_lds_bytes(q.pair.ra, q.pair.rb, q.pair.ld, lines, sizeof(cx<T>)) + (size_t)ints * sizeof(int);
+    };
+    const size_t bytes[5] = {sp.x1.pair.ra ? pair_bytes(sp.x1, sp.x1.pnl, p->NX) : xfwd_lds(sp.x1),
+                             sp.y2.pair.ra ? pair_bytes(sp.y2, sp.y2.pnl, 0) : ypass_lds(sp.y2),
+                             sp.z3.pair.ra ? pair_bytes(sp.z3, 11 * sp.z3.pnl, 0) : zpush_lds(sp.z3),
+                             sp.y4.pair.ra ? pair_bytes(sp.y4, sp.y4.pnl, 0) : ypass_lds(sp.y4),
+                             sp.x5.pair.ra ? pair_bytes(sp.x5, sp.x5.pnl, 0) : xinv_lds(sp.x5)};
     for (int k = 0; k < 5; ++k) {
       nt[k][i] = tiles[k];
       thr[k][i] = threads[k];
+      pc[k][i] = p->pair[k == 2 ? 2 : (k == 0 || k == 4) ? 0 : 1].cls;
       ls[k][i] = bytes[k];
     }
   }
   std::vector<int> starts;
-  order_pass(x1, nt[0], thr[0], ls[0], x1o, starts, b->cls[0]);
-  order_pass(y2, nt[1], thr[1], ls[1], y2o, starts, b->cls[1]);
-  order_pass(z3, nt[2], thr[2], ls[2], z3o, starts, b->cls[2]);
-  order_pass(y4, nt[3], thr[3], ls[3], y4o, starts, b->cls[3]);
-  order_pass(x5, nt[4], thr[4], ls[4], x5o, starts, b->cls[4]);
+  order_pass(x1, nt[0], thr[0], ls[0], pc[0], x1o, starts, b->cls[0]);
+  order_pass(y2, nt[1], thr[1], ls[1], pc[1], y2o, starts, b->cls[1]);
+  order_pass(z3, nt[2], thr[2], ls[2], pc[2], z3o, starts, b->cls[2]);
+  order_pass(y4, nt[3], thr[3], ls[3], pc[3], y4o, starts, b->cls[3]);
+  order_pass(x5, nt[4], thr[4], ls[4], pc[4], x5o, starts, b->cls[4]);
   for (int k = 0; k < 5; ++k) {
     b->totals[k] = 0;
     for (const auto& c : b->cls[k]) b->totals[k] += c.total;
@@ -1624,11 +1789,47 @@ BatchArgs<P> class_args(const psatd_batch* b, int k, const psatd_batch::Class& c
 // order between the fills and the merges of a step is kept by the pass order).
 template <typename T>
 void enqueue_batch_step(const psatd_batch* b, hipStream_t s) {
-  for (const auto& c : b->cls[0]) launch_xfwd_batch<T>(class_args<XFwdParams<T>>(b, 0, c), c.lds, s);
-  for (const auto& c : b->cls[1]) launch_ypass_batch<T>(class_args<YPassParams<T>>(b, 1, c), 0, c.lds, s);
-  for (const auto& c : b->cls[2]) launch_zpush_batch<T>(class_args<ZPushParams<T>>(b, 2, c), c.threads, c.lds, s);
-  for (const auto& c : b->cls[3]) launch_ypass_batch<T>(class_args<YPassParams<T>>(b, 3, c), 1, c.lds, s);
-  for (const auto& c : b->cls[4]) launch_xinv_batch<T>(class_args<XInvParams<T>>(b, 4, c), c.threads, c.lds, s);
+  // the pair kernels of batches exist for the direct and the chirp-z class of small radices
+  for (const auto& c : b->cls[0]) {
+    const auto a = class_args<XFwdParams<T>>(b, 0, c);
+    if (c.pair == 0)
+      launch_pair_xfwd_batch<T, 0>(a, c.threads, c.lds, s);
+    else if (c.pair == 2)
+      launch_pair_xfwd_batch<T, 2>(a, c.threads, c.lds, s);
+    else
+      launch_xfwd_batch<T>(a, c.lds, s);
+  }
+  auto ypass = [&](int pass, int inverse) {
+    for (const auto& c : b->cls[pass]) {
+      const auto a = class_args<YPassParams<T>>(b, pass, c);
+      if (c.pair == 0)
+        launch_pair_ypass_batch<T, 0>(a, inverse, c.threads, c.lds, s);
+      else if (c.pair == 2)
+        launch_pair_ypass_batch<T, 2>(a, inverse, c.threads, c.lds, s);
+      else
+        launch_ypass_batch<T>(a, inverse, c.lds, s);
+    }
+  };
+  ypass(1, 0);
+  for (const auto& c : b->cls[2]) {
+    const auto a = class_args<ZPushParams<T>>(b, 2, c);
+    if (c.pair == 0)
+      launch_pair_zpush_batch<T, 0>(a, c.threads, c.lds, s);
+    else if (c.pair == 2)
+      launch_pair_zpush_batch<T, 2>(a, c.threads, c.lds, s);
+    else
+      launch_zpush_batch<T>(a, c.threads, c.lds, s);
+  }
+  ypass(3, 1);
+  for (const auto& c : b->cls[4]) {
+    const auto a = class_args<XInvParams<T>>(b, 4, c);
+    if (c.pair == 0)
+      launch_pair_xinv_batch<T, 0>(a, c.threads, c.lds, s);
+    else if (c.pair == 2)
+      launch_pair_xinv_batch<T, 2>(a, c.threads, c.lds, s);
+    else
+      launch_xinv_batch<T>(a, c.threads, c.lds, s);
+  }
 }
 
 int ensure_bound(psatd_batch* b, void* const* g1) {
@@ -1797,12 +1998,9 @@ int psatd_plan_query(const psatd_plan* p, int what, long long* value) {
     case PSATD_Q_Z_COLUMNS: *value = p->zcols; break;
     case PSATD_Q_TWO_STAGE: {
       long long m = 0;
+      const int axis_of[5] = {0, 1, 2, 1, 0};
       for (int pass = 0; pass < 5; ++pass)
-        if ((p->two_stage_mask >> pass) & 1) {
-          const bool ok = p->fp64 ? has_two_stage<double>(const_cast<psatd_plan*>(p), pass)
-                                  : has_two_stage<float>(const_cast<psatd_plan*>(p), pass);
-          if (ok) m |= 1LL << pass;
-        }
+        if (p->pair[axis_of[pass]].ra) m |= 1LL << pass;
       *value = m;
       break;
     }
@@ -1849,6 +2047,15 @@ int psatd_plan_autotune(psatd_plan* p, const char* cache_path, void* stream) {
 int psatd_plan_schedule(const psatd_plan* p, int axis, int* radices, int max_radices, int* tile) {
   if (!p || !radices || !tile || axis < 0 || axis > 2) return fail(PSATD_EINVAL, "bad argument");
   const Axis& A = axis == 0 ? p->ax : (axis == 1 ? p->ay : p->az);
+  const PairAxis& q = p->pair[axis];
+  if (q.ra) {
+    const int ns = (q.ra > 1) + (q.rb > 1);
+    if (ns > max_radices) return fail(PSATD_EINVAL, "radix buffer too small");
+    if (ns > 0) radices[0] = q.ra;
+    if (ns > 1) radices[1] = q.rb;
+    *tile = pair_report_tile(p, axis);
+    return ns;
+  }
   if (A.sch.nstages > max_radices) return fail(PSATD_EINVAL, "radix buffer too small");
   for (int i = 0; i < A.sch.nstages; ++i) radices[i] = A.sch.radix[i];
   *tile = axis == 0 ? p->ty1 : (axis == 1 ? p->nl_y : p->zthreads);
@@ -2013,7 +2220,7 @@ int psatd_batch_create(int nsub, const psatd_plan_desc* subs, const int* origins
   for (int a = 0; a < 3; ++a) b->gd[a] = gdims[a];
   for (int i = 0; i < nsub; ++i) {
     psatd_plan* p = nullptr;
-    int rc = build_plan(&subs[i], &p);
+    int rc = build_plan(&subs[i], &p, false);
     if (rc == PSATD_OK) rc = check_geometry(p, origins + 3 * i, gdims);
     if (rc != PSATD_OK) {
       std::string msg = g_err;

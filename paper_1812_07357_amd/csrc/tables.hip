@@ -62,12 +62,27 @@ __global__ void k_twiddles(Tw<T>* dst, StagePlan sp) {
   }
 }
 
+// Stage B twiddles of a radix pair (see pair_fft.hpp), evaluated like the table above.
+template <typename T>
+__global__ void k_pair_twiddles(Tw<T>* dst, int ra, int rb) {
+  const int e = blockIdx.x * blockDim.x + threadIdx.x;
+  const int pitch = pair_tw_pitch(rb);
+  if (e >= ra * pitch) return;
+  const int k = e / pitch, j = e - k * pitch + 1;
+  double sn, cs;
+  sincospi(-2.0 * (double)(j * k) / (double)(ra * rb), &sn, &cs);
+  put_tw(dst, e, cs, sn);
+}
 
 // Bluestein chirp c[j] = exp(-i pi j^2 / n); j^2 is reduced modulo 2n exactly.
 template <typename T>
-__global__ void k_chirp(Tw<T>* dst, int n) {
+__global__ void k_chirp(Tw<T>* dst, int n, int count) {
   const int j = blockIdx.x * blockDim.x + threadIdx.x;
-  if (j >= n) return;
+  if (j >= count) return;
+  if (j >= n) {
+    put_tw(dst, j, 0.0, 0.0);
+    return;
+  }
   const long long q = ((long long)j * j) % (2LL * n);
   double s, c;
   sincospi(-(double)q / (double)n, &s, &c);
@@ -229,12 +244,20 @@ void launch_twiddles(void* dst, const LineSchedule& sch, int fp64, hipStream_t s
     hipLaunchKernelGGL(k_twiddles<float>, dim3(nblk(sch.n)), dim3(kT), 0, s, (Tw<float>*)dst, sp);
 }
 
-void launch_bluestein(void* chirp, void* filt, int n, int m, int fp64, hipStream_t s) {
+void launch_pair_twiddles(void* dst, int ra, int rb, int fp64, hipStream_t s) {
+  const int n = ra * pair_tw_pitch(rb);
+  if (fp64)
+    hipLaunchKernelGGL(k_pair_twiddles<double>, dim3(nblk(n)), dim3(kT), 0, s, (Tw<double>*)dst, ra, rb);
+  else
+    hipLaunchKernelGGL(k_pair_twiddles<float>, dim3(nblk(n)), dim3(kT), 0, s, (Tw<float>*)dst, ra, rb);
+}
+
+void launch_bluestein(void* chirp, int count, void* filt, int n, int m, int fp64, hipStream_t s) {
   if (fp64) {
-    hipLaunchKernelGGL(k_chirp<double>, dim3(nblk(n)), dim3(kT), 0, s, (Tw<double>*)chirp, n);
+    hipLaunchKernelGGL(k_chirp<double>, dim3(nblk(count)), dim3(kT), 0, s, (Tw<double>*)chirp, n, count);
     hipLaunchKernelGGL(k_bluestein_filter<double>, dim3(nblk(m)), dim3(kT), 0, s, (Tw<double>*)filt, n, m);
   } else {
-    hipLaunchKernelGGL(k_chirp<float>, dim3(nblk(n)), dim3(kT), 0, s, (Tw<float>*)chirp, n);
+    hipLaunchKernelGGL(k_chirp<float>, dim3(nblk(count)), dim3(kT), 0, s, (Tw<float>*)chirp, n, count);
     hipLaunchKernelGGL(k_bluestein_filter<float>, dim3(nblk(m)), dim3(kT), 0, s, (Tw<float>*)filt, n, m);
   }
 }
