@@ -419,7 +419,9 @@ typedef struct psatd_pic psatd_pic;
  * + 4 bytes per particle); for shapes 2 and 3 on grids that the tiles divide
  * with at least two tiles per axis, also one block of 5 (tile + 5)^3 values
  * per tile (52 bytes per cell in FP32 at tile 8; without that memory the
- * deposit falls back to atomics).  A tile accumulates over itself and guard cells per
+ * deposit falls back to atomics); and on collocated grids with at most two
+ * cells per particle 6 values per cell, for the gather of psatd_pic_push
+ * (without that memory it reads the six arrays).  A tile accumulates over itself and guard cells per
  * axis, one below and two above for shape 1, two below and three above for
  * shapes 2 and 3: the reach of the stencil of a particle that started in the
  * tile and moved less than a cell (tile 8: 11^3 or 13^3 cells, 53 or 88 KB of

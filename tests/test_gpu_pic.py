@@ -290,3 +290,47 @@ def test_deposit_at_scale_sampled_cells(lib, precision, shape):
         err = np.abs(got[:, cz, cy, cx] - ref[:, cz, cy, cx]).max() / scale
         assert err <= tol, ((cx, cy, cz), err)
     p.close()
+
+
+@pytest.mark.parametrize("precision", ["fp64", "fp32"])
+@pytest.mark.parametrize("shape", [1, 2, 3])
+def test_push_from_interleaved_cells_equals_the_six_arrays(lib, precision, shape):
+    """A grid large enough for the interleaved gather, an odd number of cells (a tail that no
+    16-byte vector covers) and arrays that start 4 or 8 bytes off a 16-byte boundary: the push
+    equals the one of an object that may not interleave (too few particles for its grid)
+    bit for bit, and another stream falls back to the arrays while the first still runs."""
+    import torch
+
+    gdims = (131, 77, 75) if precision == "fp32" else (101, 65, 53)
+    L = np.array(gdims, dtype=np.float64)
+    n = gdims[0] * gdims[1] * gdims[2]
+    x, u = synth.plasma_particles(synth.rng_for(171, shape), n, L, 0.5)
+    x, u = _as_inputs(x, u, precision, L)
+    p = lib.Pic(gdims, dt=0.5, q=0.1, q_over_m=-1.0, max_particles=n, precision=precision, shape=shape)
+    few = lib.Pic(gdims, dt=0.5, q=0.1, q_over_m=-1.0, max_particles=n // 4, precision=precision, shape=shape)
+    cells = torch.as_tensor(synth.random_fields(synth.rng_for(172, shape), gdims[::-1]), dtype=p.dtype, device="cuda")
+    store = torch.empty(11 * (n + 1), dtype=p.dtype, device="cuda")
+    g = [store[1 + k * (n + 1):1 + k * (n + 1) + n].view(gdims[::-1]) for k in range(11)]
+    for k in range(11):
+        g[k].copy_(cells[k])
+    a = [_gpu(v.T, p) for v in (x, u)]
+    b = [v.clone() for v in a]
+    xo = torch.empty_like(a[0])
+    p.push(g, a[0], a[1], xo)
+    for lo in range(0, n, n // 4):
+        sl = slice(lo, min(n, lo + n // 4))
+        part = [v[:, sl].contiguous() for v in b] + [xo[:, sl].clone()]
+        few.push(g, *part)
+        torch.cuda.synchronize()
+        assert torch.equal(part[0], a[0][:, sl]) and torch.equal(part[1], a[1][:, sl])
+        assert torch.equal(part[2], b[0][:, sl])
+    s1, s2 = torch.cuda.Stream(), torch.cuda.Stream()
+    c, d = [v.clone() for v in b], [v.clone() for v in b]
+    x1, x2 = torch.empty_like(xo), torch.empty_like(xo)
+    torch.cuda.synchronize()
+    p.push(g, c[0], c[1], x1, stream=s1)
+    p.push(g, d[0], d[1], x2, stream=s2)
+    torch.cuda.synchronize()
+    assert torch.equal(c[0], a[0]) and torch.equal(d[0], a[0]) and torch.equal(c[1], a[1]) and torch.equal(d[1], a[1])
+    p.close()
+    few.close()
