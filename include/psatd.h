@@ -453,8 +453,7 @@ int psatd_pic_push(psatd_pic* pic, void* const* g1, void* const* x, void* const*
  * whose order between neighbouring tiles varies from run to run; with the
  * per-tile blocks of shapes 2 and 3 (see psatd_pic_create) the blocks are
  * stored and each G1 cell sums the blocks that cover it in a fixed order.
- * A tile's particle list is built with atomics, so the rounding of the
- * per-thread sums may still vary in the last bits. */
+ * A tile's sums do not depend on the order of its particles. */
 int psatd_pic_deposit(psatd_pic* pic, void* const* g1, const void* const* x_old, const void* const* x,
                       const void* const* u, int n, void* stream);
 

@@ -44,6 +44,7 @@ namespace psatd {
 namespace {
 
 constexpr int kPicThreads = 256;
+constexpr int kXcds = 8;  // workgroups go round the chiplets in this order
 // Threads of a deposit workgroup.  Its LDS block (53 KB linear, 88 KB above) leaves one to three
 // workgroups per CU, and the particle reads through the list wait on memory: with 256 threads
 // the deposit of 33.5 M cubic particles in random order took 11.6 ms, with 1024 9.5 ms; 67 M
@@ -463,27 +464,27 @@ __global__ void __launch_bounds__(kPicThreads) k_tile_list(PicArgs<T> a, DepPtrs
   if (active) p.list[base + (int)__lane_id() - r.leader] = i;
 }
 
-// The stencil of one quantity of one particle inside the LDS block of a tile, in
-// separable form: the block-local index of its first point and the 1D weights per axis
-// (the value folded into the x weights).  The block spans E = T + Reach<K>::lo +
-// Reach<K>::hi cells per axis from the tile's first cell (bx, by, bz) minus Reach<K>::lo.
+// The stencil of one particle position inside the LDS block of a tile, in separable form: the
+// block-local index of its first point and the 1D weights per axis.  The block spans
+// E = T + Reach<K>::lo + Reach<K>::hi cells per axis from the tile's first cell (bx, by, bz)
+// minus Reach<K>::lo.
 template <int K, typename T>
 struct Axes {
   int l0;
-  T wx[K + 1], wy[K + 1], wz[K + 1];
+  T wx[K + 1];
+  double wyz[(K + 1) * (K + 1)];
 };
 
 template <int K, typename T>
-__device__ __forceinline__ void stencil_axes(Axes<K, T>& s, int E, const PicArgs<T>& a, int slot, T x, T y, T z,
-                                             T value, int bx, int by, int bz) {
-  const int ox = a.stag ? kOffStag[slot][0] : 0, oy = a.stag ? kOffStag[slot][1] : 0,
-            oz = a.stag ? kOffStag[slot][2] : 0;
+__device__ __forceinline__ void stencil_axes(Axes<K, T>& s, int E, const PicArgs<T>& a, int ox, int oy, int oz, T x,
+                                             T y, T z, int bx, int by, int bz) {
   int ix, iy, iz;
+  T wy[K + 1], wz[K + 1];
   shape1d<K>(x * a.idx - T(0.5) * ox, ix, s.wx);
-  shape1d<K>(y * a.idy - T(0.5) * oy, iy, s.wy);
-  shape1d<K>(z * a.idz - T(0.5) * oz, iz, s.wz);
+  shape1d<K>(y * a.idy - T(0.5) * oy, iy, wy);
+  shape1d<K>(z * a.idz - T(0.5) * oz, iz, wz);
 #pragma unroll
-  for (int c = 0; c <= K; ++c) s.wx[c] *= value;
+  for (int c = 0; c < (K + 1) * (K + 1); ++c) s.wyz[c] = (double)wy[c % (K + 1)] * (double)wz[c / (K + 1)];
   // local indices relative to the block origin (tile origin - guard); positions near the
   // periodic edge are taken on the tile's side of the edge.  For positions in [0, L) whose
   // particle started in the tile the first point lies in [0, E - 1 - K]; the clamp only
@@ -497,65 +498,85 @@ __device__ __forceinline__ void stencil_axes(Axes<K, T>& s, int E, const PicArgs
   s.l0 = (local(iz, bz, a.gz) * E + local(iy, by, a.gy)) * E + local(ix, bx, a.gx);
 }
 
-// The linear stencil as eight weighted values, corners in (z, y, x) order: the form the
-// run accumulation below sums in registers.
-template <typename T>
-struct Stencil {
-  int l0;
-  T w[8];
-};
-
-template <typename T>
-__device__ __forceinline__ void stencil(Stencil<T>& s, int E, const PicArgs<T>& a, int slot, T x, T y, T z,
-                                        T value, int bx, int by, int bz) {
-  Axes<1, T> g;
-  stencil_axes<1>(g, E, a, slot, x, y, z, value, bx, by, bz);
-  s.l0 = g.l0;
-#pragma unroll
-  for (int c = 0; c < 8; ++c) s.w[c] = g.wx[c & 1] * (g.wy[(c >> 1) & 1] * g.wz[c >> 2]);
-}
-
 // The LDS block accumulates in 64-bit fixed point: each weighted value times a power of two
-// `scale`, rounded to an integer, added with an integer LDS atomic (floating-point LDS
+// (its scale), rounded to an integer, added with an integer LDS atomic (floating-point LDS
 // atomics are several times slower).  Integer sums are exact and independent of their order;
 // the scale keeps every sum below 2^62 in magnitude (see k_deposit_tiles).
+//
+// The tile kernel was bound by vector instructions (0.82 per cycle and CU of at most 1 for linear
+// shapes), most of them the conversion to an integer: without it and with one stencil for the three
+// components of J the cubic kernel went from 6.1 to 5.1 ms (33.5 M particles in random order,
+// FP32), then bound by the bank conflicts of its atomics, the linear one from 4.20 to 4.04
+// (67 M, 62 steps after cell order).  A product p = w wyz of two doubles becomes one here by
+// the addition of kMagic = 1.5 * 2^52, whose sum holds p rounded to the nearest integer in its
+// low bits: with |p| < 2^51 (WORDS 1) one fma and one subtraction from the high word.  Larger p
+// (WORDS 2, w given in units of 2^32) are split exactly into a multiple of 2^32 and a rest.
 using fixed_t = unsigned long long;
+constexpr double kMagic = 6755399441055744.0;         // 1.5 * 2^52
+constexpr unsigned kMagicHi = 0x43380000u;            // its high word (the low one is 0)
+constexpr double kOneWord = 0.999 * 2251799813685248.0;  // 2^51 less a margin for the rounding of the weights
 
-template <typename T>
-__device__ __forceinline__ void stencil_add(fixed_t* blk, int E, const Stencil<T>& s, T scale) {
-#pragma unroll
-  for (int c = 0; c < 8; ++c) {
-    const long long v = llrint((double)(s.w[c] * scale));
-    atomicAdd(&blk[s.l0 + ((c >> 2) * E + ((c >> 1) & 1)) * E + (c & 1)], (fixed_t)v);
+template <int WORDS>
+__device__ __forceinline__ fixed_t to_fixed(double w, double wyz) {
+  const double t = fma(w, wyz, kMagic);
+  if constexpr (WORDS == 1) {
+    return (fixed_t)__double_as_longlong(t) - ((fixed_t)kMagicHi << 32);
+  } else {
+    const double r = fma(w, wyz, kMagic - t);
+    const fixed_t l = (fixed_t)__double_as_longlong(fma(r, 4294967296.0, kMagic));
+    const unsigned hi = (unsigned)__double_as_longlong(t) + (unsigned)(l >> 32) - kMagicHi;
+    return ((fixed_t)hi << 32) | (unsigned)l;
   }
 }
 
-// A stencil of degree K > 1 straight into the block, (K + 1)^3 atomics (its weights do not
-// fit a register run).
-template <int K, typename T>
-__device__ __forceinline__ void stencil_add_axes(fixed_t* blk, int E, const Axes<K, T>& s, T scale) {
+// The stencil times `value` (times the scale) into one quantity's block, (K + 1)^3 atomics.
+template <int K, int WORDS, typename T>
+__device__ __forceinline__ void stencil_add(fixed_t* blk, int E, const Axes<K, T>& s, T value, double scale) {
+  double w[K + 1];
+#pragma unroll
+  for (int c = 0; c <= K; ++c) w[c] = (double)(s.wx[c] * value) * scale;
 #pragma unroll
   for (int cz = 0; cz <= K; ++cz)
 #pragma unroll
     for (int cy = 0; cy <= K; ++cy) {
-      const T wyz = s.wy[cy] * s.wz[cz] * scale;
       fixed_t* row = blk + s.l0 + (cz * E + cy) * E;
 #pragma unroll
-      for (int cx = 0; cx <= K; ++cx) atomicAdd(&row[cx], (fixed_t)llrint((double)(s.wx[cx] * wyz)));
+      for (int cx = 0; cx <= K; ++cx) atomicAdd(&row[cx], to_fixed<WORDS>(w[cx], s.wyz[cz * (K + 1) + cy]));
     }
 }
 
-// Running sum of the stencils of consecutive particles of one thread: particles whose
-// stencil has the same lower corner are summed in registers, and the LDS block receives one
-// set of atomics per run (particles of one cell come in runs when the input is cell-ordered).
-template <typename T>
-__device__ __forceinline__ void stencil_run(fixed_t* blk, int E, Stencil<T>& acc, const Stencil<T>& cur, T scale) {
-  if (cur.l0 == acc.l0) {
+// The particles [e0, e1) of a tile's list into its LDS block: J at the mid-point of the step, rho_old
+// at its start and rho_new at its end.  On a collocated grid the components of J share one stencil.
+template <int K, bool STAG, int WORDS, typename T>
+__device__ __forceinline__ void deposit_run(fixed_t* lds, int E, int ncl, const PicArgs<T>& a, const DepPtrs<T>& p,
+                                            int e0, int e1, double sj, double sr, int bx, int by, int bz) {
+  const T ic2 = T(1) / (a.c * a.c);
+  const T qv = a.q * a.inv_vol;
+  for (int e = e0; e < e1; ++e) {
+    const int i = p.list[e];
+    const T u0 = p.u[0][i], u1 = p.u[1][i], u2 = p.u[2][i];
+    const T x0 = p.xo[0][i], y0 = p.xo[1][i], z0 = p.xo[2][i];
+    const T x1 = p.xn[0][i], y1 = p.xn[1][i], z1 = p.xn[2][i];
+    const T ig = T(1) / sqrt(T(1) + (u0 * u0 + u1 * u1 + u2 * u2) * ic2);
+    const T v[3] = {u0 * ig, u1 * ig, u2 * ig};
+    // mid-point (unwrapped from the start position; stencil_axes() folds the periodic edge)
+    T xm = x0 + T(0.5) * a.dt * v[0], ym = y0 + T(0.5) * a.dt * v[1], zm = z0 + T(0.5) * a.dt * v[2];
+    xm -= a.lx * floor(xm / a.lx);
+    ym -= a.ly * floor(ym / a.ly);
+    zm -= a.lz * floor(zm / a.lz);
+    Axes<K, T> g;
+    if constexpr (!STAG) stencil_axes<K>(g, E, a, 0, 0, 0, xm, ym, zm, bx, by, bz);
 #pragma unroll
-    for (int c = 0; c < 8; ++c) acc.w[c] += cur.w[c];
-  } else {
-    if (acc.l0 >= 0) stencil_add(blk, E, acc, scale);
-    acc = cur;
+    for (int k = 0; k < 3; ++k) {
+      if constexpr (STAG)  // half a cell up along its own axis
+        stencil_axes<K>(g, E, a, k == 0, k == 1, k == 2, xm, ym, zm, bx, by, bz);
+      stencil_add<K, WORDS>(lds + k * ncl, E, g, qv * v[k], sj);
+    }
+    // both charge densities live on the cell corners, staggered or not
+    stencil_axes<K>(g, E, a, 0, 0, 0, x0, y0, z0, bx, by, bz);
+    stencil_add<K, WORDS>(lds + 3 * ncl, E, g, qv, sr);
+    stencil_axes<K>(g, E, a, 0, 0, 0, x1, y1, z1, bx, by, bz);
+    stencil_add<K, WORDS>(lds + 4 * ncl, E, g, qv, sr);
   }
 }
 
@@ -563,7 +584,7 @@ __device__ __forceinline__ void stencil_run(fixed_t* blk, int E, Stencil<T>& acc
 // (end) into LDS over the tile and its guard cells, then the block either added into G1
 // with global atomics (blocks == nullptr) or stored whole, tile by tile, into `blocks`
 // ([tile][quantity][z][y][x], E^3 values per quantity) for k_gather_blocks.
-template <typename T, int K>
+template <typename T, int K, bool STAG>
 __global__ void __launch_bounds__(kDepositThreads<K>) k_deposit_tiles(PicArgs<T> a, DepPtrs<T> p, T* __restrict__ blocks) {
   extern __shared__ double2 pic_smem[];
   fixed_t* lds = reinterpret_cast<fixed_t*>(pic_smem);
@@ -579,65 +600,23 @@ __global__ void __launch_bounds__(kDepositThreads<K>) k_deposit_tiles(PicArgs<T>
     const int bx = tx * a.tile, by = ty * a.tile, bz = tz * a.tile;
     for (int i = tid; i < 5 * ncl; i += blockDim.x) lds[i] = 0;
     __syncthreads();
-    const T ic2 = T(1) / (a.c * a.c);
-    const T qv = a.q * a.inv_vol;
     // each thread takes a contiguous run of the tile's list, so the lanes of a wave work in
-    // different cells (no two lanes add to one LDS word in the same instruction) and one
-    // thread's consecutive particles share stencils
+    // different cells: no two lanes add to one LDS word in the same instruction
     const int first = p.offset[t], count = p.offset[t + 1] - first;
     // fixed-point scales of J and rho: a particle adds at most |q| c / V (|v| < c) to a J
     // point and |q| / V to a rho point, so with count particles every sum stays below
     // count * bound * scale < 2^62.  Powers of two: scaling and unscaling are exact.
-    const double bq = fabs((double)a.q) * (double)a.inv_vol * (double)max(count, 1);
-    const int ej = 61 - ilogb(fmax(bq * (double)a.c * 1.0000001, 1e-300));
-    const int er = 61 - ilogb(fmax(bq * 1.0000001, 1e-300));
+    const double bv = fabs((double)a.q) * (double)a.inv_vol * 1.0000001, bj = bv * (double)a.c;
+    const double nmax = (double)max(count, 1);
     // (capped where the bound is tiny: then bound * 2^120 is below 2^62 anyway)
-    const int ejc = min(ej, 120), erc = min(er, 120);
-    const T sj = (T)ldexp(1.0, ejc), sr = (T)ldexp(1.0, erc);
+    const int ejc = min(61 - ilogb(fmax(bj * nmax, 1e-300)), 120), erc = min(61 - ilogb(fmax(bv * nmax, 1e-300)), 120);
     const int per = (count + (int)blockDim.x - 1) / (int)blockDim.x;
     const int e0 = first + min(count, tid * per), e1 = first + min(count, (tid + 1) * per);
-    Stencil<T> acc[K == 1 ? 5 : 1], cur;
-#pragma unroll
-    for (int q = 0; q < (K == 1 ? 5 : 1); ++q) acc[q].l0 = -1;
-    for (int e = e0; e < e1; ++e) {
-      const int i = p.list[e];
-      const T u0 = p.u[0][i], u1 = p.u[1][i], u2 = p.u[2][i];
-      const T ig = T(1) / sqrt(T(1) + (u0 * u0 + u1 * u1 + u2 * u2) * ic2);
-      const T v[3] = {u0 * ig, u1 * ig, u2 * ig};
-      const T x0 = p.xo[0][i], y0 = p.xo[1][i], z0 = p.xo[2][i];
-      // mid-point (unwrapped from the start position; stencil() folds the periodic edge)
-      T xm = x0 + T(0.5) * a.dt * v[0], ym = y0 + T(0.5) * a.dt * v[1], zm = z0 + T(0.5) * a.dt * v[2];
-      xm -= a.lx * floor(xm / a.lx);
-      ym -= a.ly * floor(ym / a.ly);
-      zm -= a.lz * floor(zm / a.lz);
-      if constexpr (K == 1) {
-#pragma unroll
-        for (int k = 0; k < 3; ++k) {
-          stencil(cur, E, a, 6 + k, xm, ym, zm, qv * v[k], bx, by, bz);
-          stencil_run(lds + k * ncl, E, acc[k], cur, sj);
-        }
-        stencil(cur, E, a, 9, x0, y0, z0, qv, bx, by, bz);
-        stencil_run(lds + 3 * ncl, E, acc[3], cur, sr);
-        stencil(cur, E, a, 10, p.xn[0][i], p.xn[1][i], p.xn[2][i], qv, bx, by, bz);
-        stencil_run(lds + 4 * ncl, E, acc[4], cur, sr);
-      } else {
-        Axes<K, T> g;
-#pragma unroll
-        for (int k = 0; k < 3; ++k) {
-          stencil_axes<K>(g, E, a, 6 + k, xm, ym, zm, qv * v[k], bx, by, bz);
-          stencil_add_axes<K>(lds + k * ncl, E, g, sj);
-        }
-        stencil_axes<K>(g, E, a, 9, x0, y0, z0, qv, bx, by, bz);
-        stencil_add_axes<K>(lds + 3 * ncl, E, g, sr);
-        stencil_axes<K>(g, E, a, 10, p.xn[0][i], p.xn[1][i], p.xn[2][i], qv, bx, by, bz);
-        stencil_add_axes<K>(lds + 4 * ncl, E, g, sr);
-      }
-    }
-    if constexpr (K == 1) {
-#pragma unroll
-      for (int q = 0; q < 5; ++q)
-        if (acc[q].l0 >= 0) stencil_add(lds + q * ncl, E, acc[q], q < 3 ? sj : sr);
-    }
+    // one word where a single value stays below 2^51, which is from about 2050 particles on
+    if (ldexp(bj, ejc) < kOneWord && ldexp(bv, erc) < kOneWord)
+      deposit_run<K, STAG, 1>(lds, E, ncl, a, p, e0, e1, ldexp(1.0, ejc), ldexp(1.0, erc), bx, by, bz);
+    else
+      deposit_run<K, STAG, 2>(lds, E, ncl, a, p, e0, e1, ldexp(1.0, ejc - 32), ldexp(1.0, erc - 32), bx, by, bz);
     __syncthreads();
     if (blocks) {
       // the whole block, unscaled, in the tile's slot (consecutive threads, consecutive words)
@@ -692,13 +671,15 @@ __global__ void __launch_bounds__(kDepositThreads<K>) k_deposit_tiles(PicArgs<T>
 // than a tile, so that along each axis a cell is reached by its own tile and at most one
 // neighbour (with two tiles per axis both neighbours are the same tile, reached through one
 // face or the other).  Every cell is written (no zeroing first), with a fixed order of the
-// sums.
+// sums.  Each chiplet takes one range of tiles, so that neighbours along x find their common lines in
+// one L2 (4.2 M cells, FP32: 0.206 -> 0.143 ms).
 template <typename T, int K>
 __global__ void __launch_bounds__(256) k_gather_blocks(PicArgs<T> a, DepPtrs<T> p, const T* __restrict__ blocks) {
   constexpr int GL = Reach<K>::lo, GH = Reach<K>::hi;
   const int T_ = a.tile, E = T_ + GL + GH, T2 = T_ * T_;
   const long long ncl = (long long)E * E * E;
-  const int tile = blockIdx.x;
+  const int per = gridDim.x / kXcds, tile = blockIdx.x % kXcds * per + blockIdx.x / kXcds;
+  if (tile >= a.ntiles) return;
   const int tz = tile / (a.tx * a.ty), ty = (tile - tz * a.tx * a.ty) / a.tx, tx = tile - (tz * a.ty + ty) * a.tx;
   // per axis: the tiles whose block covers local cell c, and the cell's index in each
   auto reach = [&](int c, int t, int nt, int* ts, int* ls) {
@@ -706,13 +687,13 @@ __global__ void __launch_bounds__(256) k_gather_blocks(PicArgs<T> a, DepPtrs<T> 
     ls[0] = c + GL;
     int m = 1;
     if (c < GH) {  // in the upper guard of the tile below
-      ts[m] = t == 0 ? nt - 1 : t - 1;
-      ls[m] = c + T_ + GL;
-      ++m;
+      ts[1] = t == 0 ? nt - 1 : t - 1;
+      ls[1] = c + T_ + GL;
+      m = 2;
     } else if (c >= T_ - GL) {  // in the lower guard of the tile above
-      ts[m] = t == nt - 1 ? 0 : t + 1;
-      ls[m] = c - T_ + GL;
-      ++m;
+      ts[1] = t == nt - 1 ? 0 : t + 1;
+      ls[1] = c - T_ + GL;
+      m = 2;
     }
     return m;
   };
@@ -723,13 +704,24 @@ __global__ void __launch_bounds__(256) k_gather_blocks(PicArgs<T> a, DepPtrs<T> 
               mz = reach(lz, tz, a.tz, tsz, lsz);
     T acc[5] = {0, 0, 0, 0, 0};
     for (int iz = 0; iz < mz; ++iz)
-      for (int iy = 0; iy < my; ++iy)
-        for (int ix = 0; ix < mx; ++ix) {
-          const long long t = ((long long)tsz[iz] * a.ty + tsy[iy]) * a.tx + tsx[ix];
-          const T* b = blocks + t * 5 * ncl + ((long long)lsz[iz] * E + lsy[iy]) * E + lsx[ix];
+      for (int iy = 0; iy < my; ++iy) {
+        const long long row = ((long long)tsz[iz] * a.ty + tsy[iy]) * a.tx;
+        const int r = (lsz[iz] * E + lsy[iy]) * E;
+        const T* b0 = blocks + (row + tsx[0]) * 5 * ncl + r + lsx[0];
+        T v[5];
 #pragma unroll
-          for (int f = 0; f < 5; ++f) acc[f] += b[f * ncl];
+        for (int f = 0; f < 5; ++f) v[f] = b0[f * ncl];
+        if (mx == 2) {
+          const T* b1 = blocks + (row + tsx[1]) * 5 * ncl + r + lsx[1];
+          T w[5];
+#pragma unroll
+          for (int f = 0; f < 5; ++f) w[f] = b1[f * ncl];
+#pragma unroll
+          for (int f = 0; f < 5; ++f) v[f] += w[f];
         }
+#pragma unroll
+        for (int f = 0; f < 5; ++f) acc[f] += v[f];
+      }
     const long long cell = ((long long)(tz * T_ + lz) * a.gy + (ty * T_ + ly)) * a.gx + (tx * T_ + lx);
 #pragma unroll
     for (int f = 0; f < 5; ++f) p.g[f][cell] = acc[f];
@@ -879,15 +871,23 @@ int pic_push(psatd_pic* o, void* const* g1, void* const* x, void* const* u, void
   return PSATD_OK;
 }
 
-template <typename T, int K>
-void launch_deposit(const PicArgs<T>& a, const DepPtrs<T>& p, T* blocks, size_t lds, hipStream_t s) {
+template <typename T, int K, bool STAG>
+void launch_tiles(const PicArgs<T>& a, const DepPtrs<T>& p, T* blocks, size_t lds, hipStream_t s) {
   if (lds > 64 * 1024)
-    (void)hipFuncSetAttribute((const void*)k_deposit_tiles<T, K>, hipFuncAttributeMaxDynamicSharedMemorySize,
+    (void)hipFuncSetAttribute((const void*)k_deposit_tiles<T, K, STAG>, hipFuncAttributeMaxDynamicSharedMemorySize,
                               (int)lds);
   // one tile per workgroup (the loop inside covers grids beyond the cap)
   const unsigned grid = (unsigned)std::min(a.ntiles, 1 << 20);
-  hipLaunchKernelGGL((k_deposit_tiles<T, K>), dim3(grid), dim3(kDepositThreads<K>), lds, s, a, p, blocks);
-  if (blocks) hipLaunchKernelGGL((k_gather_blocks<T, K>), dim3(a.ntiles), dim3(256), 0, s, a, p, (const T*)blocks);
+  hipLaunchKernelGGL((k_deposit_tiles<T, K, STAG>), dim3(grid), dim3(kDepositThreads<K>), lds, s, a, p, blocks);
+}
+template <typename T, int K>
+void launch_deposit(const PicArgs<T>& a, const DepPtrs<T>& p, T* blocks, size_t lds, hipStream_t s) {
+  if (a.stag)
+    launch_tiles<T, K, true>(a, p, blocks, lds, s);
+  else
+    launch_tiles<T, K, false>(a, p, blocks, lds, s);
+  if (blocks) hipLaunchKernelGGL((k_gather_blocks<T, K>), dim3((a.ntiles + kXcds - 1) / kXcds * kXcds), dim3(256), 0, s, a, p,
+                                 (const T*)blocks);
 }
 
 template <typename T>
@@ -985,7 +985,7 @@ int psatd_pic_create(const psatd_pic_desc* d, psatd_pic** out) {
   // with atomics.
   {
     const int shape = shape_of(*d), T = d->tile;
-    const int reach = Reach<2>::lo + Reach<2>::hi;
+    const int reach = shape == 1 ? Reach<1>::lo + Reach<1>::hi : Reach<2>::lo + Reach<2>::hi;
     const bool tiled = shape >= 2 && d->gx % T == 0 && d->gy % T == 0 && d->gz % T == 0 && o->tx >= 2 &&
                        o->ty >= 2 && o->tz >= 2 && reach <= T;
     if (tiled) {

@@ -334,3 +334,19 @@ def test_push_from_interleaved_cells_equals_the_six_arrays(lib, precision, shape
     assert torch.equal(c[0], a[0]) and torch.equal(d[0], a[0]) and torch.equal(c[1], a[1]) and torch.equal(d[1], a[1])
     p.close()
     few.close()
+
+
+@pytest.mark.parametrize("precision", ["fp64", "fp32"])
+@pytest.mark.parametrize("staggered", [False, True])
+@pytest.mark.parametrize("gdims,tile,n,shape", [
+    ((64, 48, 40), 1, 60000, 1),  # 122880 tiles: more than a table holds, in random order
+    ((64, 48, 40), 1, 1, 3),
+    ((64, 48, 40), 1, 4097, 2),  # one particle more than a workgroup's fill
+    ((16, 16, 16), 8, 16400, 1),  # 2050 particles a tile: some tiles in one word, some in two
+    ((16, 16, 16), 8, 30000, 3),  # one word
+    ((16, 16, 16), 8, 9, 2),  # two words
+])
+def test_deposit_tables_and_fixed_point_words(lib, precision, staggered, gdims, tile, n, shape):
+    got, _, ref = _deposit_case(lib, precision, staggered, gdims, tile, n, 173, shape)
+    tol = 1e-12 if precision == "fp64" else 2e-5
+    assert np.abs(got[6:] - ref).max() / np.abs(ref).max() <= tol
