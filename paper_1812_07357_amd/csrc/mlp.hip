@@ -13,9 +13,13 @@
 //
 // Weights live twice: an FP32 master copy that Adam updates and a bfloat16
 // copy (round to nearest, ties to even) that the forward and backward kernels
-// read.  Activations, products and sums are FP32.  The 64-wide layers are far
-// too small for matrix-core tiles to pay at these batch sizes, so the products
-// are FP32 FMAs on LDS-resident tiles.
+// read.  Activations, products and sums are FP32: the products are FP32 matrix
+// instructions (16x16x4) on tiles of 16 samples.  Calls are small, so each
+// kernel is a chain of latencies and not of rates.  Weights go from memory into the
+// operand registers of their wave, without LDS, and only what crosses waves
+// (inputs, h1, dz2) passes through LDS.  With FMAs on LDS tiles of 32 samples 12
+// predictions took 8.6 us of kernel time (now 3.4) and a gradient over 512 samples 18.3 + 5.1
+// for its two kernels (now 7.2 + 2.7).
 //
 // Parameter vector (a documented format): W1 (64 x 6, row-major out x in), b1,
 // W2 (64 x 64), b2, W3 (64), b3 -- 4673 values.
@@ -25,6 +29,7 @@
 
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cmath>
 #include <cstdint>
 #include <cstring>
@@ -38,10 +43,13 @@ constexpr int NIN = 6, NH = 64;
 constexpr int OFF_W1 = 0, OFF_B1 = OFF_W1 + NH * NIN, OFF_W2 = OFF_B1 + NH, OFF_B2 = OFF_W2 + NH * NH,
               OFF_W3 = OFF_B2 + NH, OFF_B3 = OFF_W3 + NH, NPARAM = OFF_B3 + 1;
 static_assert(NPARAM == PSATD_MLP_NPARAM, "parameter count");
-constexpr int TS = 32;       // samples per tile (one tile per block)
-constexpr int NT = 256;      // threads per block
-constexpr int LD = NH + 1;   // padded row length of the LDS activation tiles
-constexpr int SB = TS / 16;  // sample rows per thread in the (sample, unit) mappings
+constexpr int TS = 16;       // samples per tile
+constexpr int NT = 256;      // threads per block: four waves, 16 units of a layer each
+constexpr int LD = NH + 4;   // padded row length of the LDS tiles: operand reads without bank conflicts
+constexpr int XP = 8;        // padded row length of the inputs
+// A block walks every gridDim-th tile with its weights in registers.  One partial gradient
+// per block bounds what the second kernel reads; 256 CUs hold two blocks of the gradient each.
+constexpr int kGradBlocks = 512, kForwardBlocks = 2048;
 
 struct Norm {
   float in_mean[NIN];
@@ -60,216 +68,272 @@ __host__ __device__ inline uint16_t f32_to_bf16(float f) {
   return (uint16_t)(u >> 16);
 }
 
-__device__ __forceinline__ float silu_f(float z) { return z / (1.0f + expf(-z)); }
-__device__ __forceinline__ float silu_d(float z) {
-  const float s = 1.0f / (1.0f + expf(-z));
-  return s * (1.0f + z * (1.0f - s));
+// silu(z) and its derivative
+__device__ __forceinline__ float silu(float z, float& d) {
+  const float q = 1.0f + expf(-z), s = 1.0f / q;
+  d = s * (1.0f + z * (1.0f - s));
+  return z / q;
+}
+
+typedef float f4 __attribute__((ext_vector_type(4)));
+
+// D = A B + C with A 16x4 (lane l: row l % 16, column l / 16), B 4x16 (lane l: row l / 16, column
+// l % 16), C and D 16x16 (lane l: rows 4 (l / 16) + 0..3, column l % 16).  The four columns of A and
+// rows of B of one instruction are any four of the inner index, as long as both agree.
+__device__ __forceinline__ f4 mfma(float a, float b, f4 c) {
+  return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
 }
 
 struct Tile {
-  float w1[NH * NIN], b1[NH], w2[NH * LD], b2[NH], w3[NH], b3;
-  float x[TS * NIN], t[TS], valid[TS], dy[TS], lossv[TS];
-  float h1[TS * LD], d1[TS * LD], h2[TS * LD], d2[TS * LD];
+  float x[TS * XP];  // standardised inputs, column 6 one and column 7 zero
+  float t[TS], valid[TS];
+  float u[4 * TS];   // the output's sums over the units of each wave
+  alignas(16) float h1[TS * LD];
+  alignas(16) float dz[TS * LD];
 };
 
-// Stage weights and the tile's (standardised) inputs; samples past the batch
-// or with an out-of-range index are masked out (valid = 0, inputs 0).
-__device__ void load_tile(Tile& L, const uint16_t* __restrict__ w, const float* __restrict__ X,
-                          const float* __restrict__ tgt, int n, const int* __restrict__ idx, int first, int count,
-                          const Norm& nm) {
-  const int tid = threadIdx.x;
-  for (int i = tid; i < NH * NIN; i += NT) L.w1[i] = bf16_to_f32(w[OFF_W1 + i]);
-  for (int i = tid; i < NH * NH; i += NT) L.w2[(i >> 6) * LD + (i & 63)] = bf16_to_f32(w[OFF_W2 + i]);
-  if (tid < NH) {
-    L.b1[tid] = bf16_to_f32(w[OFF_B1 + tid]);
-    L.b2[tid] = bf16_to_f32(w[OFF_B2 + tid]);
-    L.w3[tid] = bf16_to_f32(w[OFF_W3 + tid]);
+// Lane l of wave w holds unit n = 16 w + l % 16 and the inner range of group g = l / 16.
+struct Weights {
+  float w1[2];   // W1[n][2 g + 0..1], zero for g = 3
+  float w2[16];  // W2[n][16 g + 0..15]
+  float b1, b2, w3, b3;
+};
+__device__ __forceinline__ void load_weights(Weights& q, const uint16_t* __restrict__ w, int n, int g) {
+  const uint32_t p = g < 3 ? *reinterpret_cast<const uint32_t*>(w + OFF_W1 + n * NIN + 2 * g) : 0u;
+  const uint4 a = *reinterpret_cast<const uint4*>(w + OFF_W2 + n * NH + 16 * g),
+              b = *reinterpret_cast<const uint4*>(w + OFF_W2 + n * NH + 16 * g + 8);
+  q.w1[0] = __uint_as_float(p << 16);
+  q.w1[1] = __uint_as_float(p & 0xffff0000u);
+  const uint32_t v[8] = {a.x, a.y, a.z, a.w, b.x, b.y, b.z, b.w};
+#pragma unroll
+  for (int k = 0; k < 8; ++k) {
+    q.w2[2 * k] = __uint_as_float(v[k] << 16);
+    q.w2[2 * k + 1] = __uint_as_float(v[k] & 0xffff0000u);
   }
-  if (tid == 0) L.b3 = bf16_to_f32(w[OFF_B3]);
-  if (tid < TS) {
-    const int b = first + tid;  // position in the batch
+  q.b1 = bf16_to_f32(w[OFF_B1 + n]);
+  q.b2 = bf16_to_f32(w[OFF_B2 + n]);
+  q.w3 = bf16_to_f32(w[OFF_W3 + n]);
+  q.b3 = bf16_to_f32(w[OFF_B3]);
+}
+static_assert(OFF_W1 % 2 == 0 && NIN % 2 == 0 && OFF_W2 % 8 == 0 && NH % 8 == 0, "alignment of the vector loads");
+
+// The tile's standardised inputs; samples past the batch or with an out-of-range index are masked
+// out (valid = 0, inputs 0).
+__device__ __forceinline__ void load_tile(Tile& L, const float* __restrict__ X, const float* __restrict__ tgt, int n,
+                                          const int* __restrict__ idx, int first, int count, const Norm& nm) {
+  const int tid = threadIdx.x;
+  if (tid < TS * XP) {
+    const int m = tid / XP, k = tid % XP, b = first + m;  // b: position in the batch
     int s = -1;
     if (b < count) s = idx ? idx[b] : b;
     const bool ok = s >= 0 && s < n;
-    L.valid[tid] = ok ? 1.0f : 0.0f;
-    for (int k = 0; k < NIN; ++k)
-      L.x[tid * NIN + k] = ok ? (X[(size_t)s * NIN + k] - nm.in_mean[k]) * nm.in_scale[k] : 0.0f;
-    L.t[tid] = (ok && tgt) ? (tgt[s] - nm.out_mean) / nm.out_scale : 0.0f;
+    float mean = nm.in_mean[0], scale = nm.in_scale[0];
+#pragma unroll
+    for (int c = 1; c < NIN; ++c)
+      if (k == c) {
+        mean = nm.in_mean[c];
+        scale = nm.in_scale[c];
+      }
+    float v = k == NIN ? 1.0f : 0.0f;
+    if (k < NIN) v = ok ? (X[(size_t)s * NIN + k] - mean) * scale : 0.0f;
+    L.x[tid] = v;
+    if (k == XP - 1) {
+      L.valid[m] = ok ? 1.0f : 0.0f;
+      L.t[m] = (ok && tgt) ? (tgt[s] - nm.out_mean) / nm.out_scale : 0.0f;
+    }
   }
-  __syncthreads();
 }
 
-// h1, h2 (and silu' of their pre-activations) for the tile; returns u for sample tid < TS in u_out.
-__device__ void forward_tile(Tile& L, float* u_out) {
-  const int tid = threadIdx.x;
-  const int sb = tid >> 4, jb = tid & 15;
+// Sum over the 16 lanes of a group, in every lane.
+__device__ __forceinline__ float group_sum(float v) {
 #pragma unroll
-  for (int b = 0; b < SB; ++b) {
-    const int s = sb + 16 * b;
+  for (int d = 1; d < 16; d <<= 1) v += __shfl_xor(v, d);
+  return v;
+}
+// Sum over the four groups, in every lane.
+__device__ __forceinline__ float across_groups(float v) {
+  v += __shfl_xor(v, 16);
+  return v + __shfl_xor(v, 32);
+}
+
+// 16 floats of an LDS row from 16 g on, the A operands of the 16 products over 64 inner indices
+__device__ __forceinline__ void load_row(float* a, const float* row) {
 #pragma unroll
-    for (int a = 0; a < 4; ++a) {
-      const int j = jb + 16 * a;
-      float z = L.b1[j];
+  for (int k = 0; k < 4; ++k) {
+    const f4 v = *reinterpret_cast<const f4*>(row + 4 * k);
 #pragma unroll
-      for (int k = 0; k < NIN; ++k) z = fmaf(L.w1[j * NIN + k], L.x[s * NIN + k], z);
-      L.h1[s * LD + j] = silu_f(z);
-      L.d1[s * LD + j] = silu_d(z);
-    }
+    for (int c = 0; c < 4; ++c) a[4 * k + c] = v[c];
+  }
+}
+
+// Samples 4 g + 0..3 of unit n: h1, h2 and the derivatives of their silu; u (of the same samples) and
+// h1 also through LDS.  Starts once the tile's inputs are written (barrier inside).
+__device__ __forceinline__ void forward_tile(Tile& L, const Weights& q, int wave, int c, int g, f4& h1, f4& d1, f4& h2,
+                                             f4& d2, f4& u) {
+  __syncthreads();
+  f4 z = {q.b1, q.b1, q.b1, q.b1};
+#pragma unroll
+  for (int j = 0; j < 2; ++j) z = mfma(L.x[c * XP + 2 * g + j], q.w1[j], z);
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    float d;
+    h1[i] = silu(z[i], d);
+    d1[i] = d;
+    L.h1[(4 * g + i) * LD + 16 * wave + c] = h1[i];
   }
   __syncthreads();
-  float acc[SB][4];
+  float a[16];
+  load_row(a, L.h1 + c * LD + 16 * g);
+  // two sums, so that each product waits for the one before the last
+  f4 za = {q.b2, q.b2, q.b2, q.b2}, zb = {0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
-  for (int b = 0; b < SB; ++b)
-#pragma unroll
-    for (int a = 0; a < 4; ++a) acc[b][a] = L.b2[jb + 16 * a];
-  for (int i = 0; i < NH; ++i) {
-    float hv[SB], wv[4];
-#pragma unroll
-    for (int b = 0; b < SB; ++b) hv[b] = L.h1[(sb + 16 * b) * LD + i];
-#pragma unroll
-    for (int a = 0; a < 4; ++a) wv[a] = L.w2[(jb + 16 * a) * LD + i];
-#pragma unroll
-    for (int b = 0; b < SB; ++b)
-#pragma unroll
-      for (int a = 0; a < 4; ++a) acc[b][a] = fmaf(wv[a], hv[b], acc[b][a]);
+  for (int j = 0; j < 16; j += 2) {
+    za = mfma(a[j], q.w2[j], za);
+    zb = mfma(a[j + 1], q.w2[j + 1], zb);
   }
 #pragma unroll
-  for (int b = 0; b < SB; ++b)
-#pragma unroll
-    for (int a = 0; a < 4; ++a) {
-      const int s = sb + 16 * b, j = jb + 16 * a;
-      L.h2[s * LD + j] = silu_f(acc[b][a]);
-      L.d2[s * LD + j] = silu_d(acc[b][a]);
-    }
+  for (int i = 0; i < 4; ++i) {
+    float d;
+    h2[i] = silu(za[i] + zb[i], d);
+    d2[i] = d;
+    const float p = group_sum(q.w3 * h2[i]);
+    if (c == 0) L.u[wave * TS + 4 * g + i] = p;
+  }
   __syncthreads();
-  if (tid < TS) {
-    float u = L.b3;
-    for (int j = 0; j < NH; ++j) u = fmaf(L.w3[j], L.h2[tid * LD + j], u);
-    *u_out = u;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const int m = 4 * g + i;
+    u[i] = q.b3 + ((L.u[m] + L.u[TS + m]) + (L.u[2 * TS + m] + L.u[3 * TS + m]));
   }
 }
 
 __global__ void __launch_bounds__(NT) k_mlp_forward(const uint16_t* __restrict__ w, const float* __restrict__ X,
                                                      int n, float* __restrict__ y, Norm nm) {
   __shared__ Tile L;
-  const int first = blockIdx.x * TS;
-  load_tile(L, w, X, nullptr, n, nullptr, first, n, nm);
-  float u = 0.0f;
-  forward_tile(L, &u);
-  const int tid = threadIdx.x;
-  if (tid < TS && first + tid < n) y[first + tid] = nm.out_mean + nm.out_scale * u;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, c = lane & 15, g = lane >> 4;
+  Weights q;
+  load_weights(q, w, 16 * wave + c, g);
+  for (int tile = blockIdx.x; tile <= (n - 1) / TS; tile += gridDim.x) {
+    const int first = tile * TS;
+    load_tile(L, X, nullptr, n, nullptr, first, n, nm);
+    f4 h1, d1, h2, d2, u;
+    forward_tile(L, q, wave, c, g, h1, d1, h2, d2, u);
+    // (the inputs of the next tile are written after the last barrier that follows their last read)
+    if (wave == 0 && c == 0)
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+        if (first + 4 * g + i < n) y[first + 4 * g + i] = nm.out_mean + nm.out_scale * u[i];
+  }
 }
 
-// Partial MSE gradient of one tile of the batch (batch positions first .. first+TS-1).
+// Partial MSE gradient of a block's tiles of the batch.
 __global__ void __launch_bounds__(NT) k_mlp_grad(const uint16_t* __restrict__ w, const float* __restrict__ X,
                                                   const float* __restrict__ tgt, int n, const int* __restrict__ idx,
                                                   int count, float* __restrict__ part, float* __restrict__ lossp,
                                                   Norm nm) {
   __shared__ Tile L;
-  const int tid = threadIdx.x;
-  const int first = blockIdx.x * TS;
-  load_tile(L, w, X, tgt, n, idx, first, count, nm);
-  float u = 0.0f;
-  forward_tile(L, &u);
-  if (tid < TS) {
-    const float r = (u - L.t[tid]) * L.valid[tid];
-    L.dy[tid] = 2.0f * r / (float)count;
-    L.lossv[tid] = r * r;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, c = lane & 15, g = lane >> 4;
+  const int unit = 16 * wave + c;
+  Weights q;
+  load_weights(q, w, unit, g);
+  float w2t[16];  // W2[16 g + 0..15][n]
+#pragma unroll
+  for (int j = 0; j < 16; ++j) w2t[j] = bf16_to_f32(w[OFF_W2 + (16 * g + j) * NH + unit]);
+  const f4 zero = {0.0f, 0.0f, 0.0f, 0.0f};
+  f4 gw2[4] = {zero, zero, zero, zero};  // dW2 of rows 16 wave + 4 g + 0..3, columns c + 16 k
+  f4 gw1 = zero;                         // dW1 of the same rows, column c; column 6 is db1
+  float gb2 = 0.0f, gw3 = 0.0f, gb3 = 0.0f, loss = 0.0f;
+  for (int tile = blockIdx.x; tile <= (count - 1) / TS; tile += gridDim.x) {
+    const int first = tile * TS;
+    load_tile(L, X, tgt, n, idx, first, count, nm);
+    f4 h1, d1, h2, d2, u, dz2;
+    forward_tile(L, q, wave, c, g, h1, d1, h2, d2, u);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int m = 4 * g + i;
+      const float r = (u[i] - L.t[m]) * L.valid[m];
+      const float dy = 2.0f * r / (float)count;
+      loss += r * r;
+      gb3 += dy;
+      gw3 = fmaf(dy, h2[i], gw3);
+      dz2[i] = dy * q.w3 * d2[i];
+      gb2 += dz2[i];
+      L.dz[m * LD + unit] = dz2[i];
+    }
+    // dW2[j][i] += sum over samples of dz2[s][j] h1[s][i]
+#pragma unroll
+    for (int k = 0; k < 4; ++k)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) gw2[k] = mfma(dz2[i], L.h1[(4 * g + i) * LD + 16 * k + c], gw2[k]);
+    __syncthreads();
+    // dz1[s][i] = silu'(z1[s][i]) sum over j of W2[j][i] dz2[s][j]
+    float a[16];
+    load_row(a, L.dz + c * LD + 16 * g);
+    f4 sa = zero, sb = zero;
+#pragma unroll
+    for (int j = 0; j < 16; j += 2) {
+      sa = mfma(a[j], w2t[j], sa);
+      sb = mfma(a[j + 1], w2t[j + 1], sb);
+    }
+    // dW1[j][k] += sum over samples of dz1[s][j] x[s][k]
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+      gw1 = mfma(d1[i] * (sa[i] + sb[i]), c < XP ? L.x[(4 * g + i) * XP + c] : 0.0f, gw1);
+    __syncthreads();  // the next tile's inputs overwrite these
   }
-  __syncthreads();
-  float* g = part + (size_t)blockIdx.x * NPARAM;
-  const int sb = tid >> 4, jb = tid & 15;
-  // dz2 = dy * W3 * silu'(z2), in place of silu'(z2)
+  float* out = part + (size_t)blockIdx.x * NPARAM;
 #pragma unroll
-  for (int b = 0; b < SB; ++b)
+  for (int i = 0; i < 4; ++i) {
+    const int j = 16 * wave + 4 * g + i;
 #pragma unroll
-    for (int a = 0; a < 4; ++a) {
-      const int s = sb + 16 * b, j = jb + 16 * a;
-      L.d2[s * LD + j] *= L.dy[s] * L.w3[j];
-    }
-  __syncthreads();
-  // dW2[j][i] = sum_s dz2[s][j] h1[s][i]   (thread: j = jb + 16a, i = ib + 16c)
-  {
-    const int ib = tid >> 4;
-    float acc[4][4] = {};
-    for (int s = 0; s < TS; ++s) {
-      float dv[4], hv[4];
-#pragma unroll
-      for (int a = 0; a < 4; ++a) dv[a] = L.d2[s * LD + jb + 16 * a];
-#pragma unroll
-      for (int c = 0; c < 4; ++c) hv[c] = L.h1[s * LD + ib + 16 * c];
-#pragma unroll
-      for (int a = 0; a < 4; ++a)
-#pragma unroll
-        for (int c = 0; c < 4; ++c) acc[a][c] = fmaf(dv[a], hv[c], acc[a][c]);
-    }
-#pragma unroll
-    for (int a = 0; a < 4; ++a)
-#pragma unroll
-      for (int c = 0; c < 4; ++c) g[OFF_W2 + (jb + 16 * a) * NH + ib + 16 * c] = acc[a][c];
+    for (int k = 0; k < 4; ++k) out[OFF_W2 + j * NH + 16 * k + c] = gw2[k][i];
+    if (c < NIN) out[OFF_W1 + j * NIN + c] = gw1[i];
+    if (c == NIN) out[OFF_B1 + j] = gw1[i];
   }
-  // dz1[s][i] = silu'(z1[s][i]) * sum_j W2[j][i] dz2[s][j], in place of silu'(z1)
-  {
-    const int ib = tid & 15;
-    float acc[SB][4] = {};
-    for (int j = 0; j < NH; ++j) {
-      float dv[SB], wv[4];
-#pragma unroll
-      for (int b = 0; b < SB; ++b) dv[b] = L.d2[(sb + 16 * b) * LD + j];
-#pragma unroll
-      for (int c = 0; c < 4; ++c) wv[c] = L.w2[j * LD + ib + 16 * c];
-#pragma unroll
-      for (int b = 0; b < SB; ++b)
-#pragma unroll
-        for (int c = 0; c < 4; ++c) acc[b][c] = fmaf(wv[c], dv[b], acc[b][c]);
-    }
-#pragma unroll
-    for (int b = 0; b < SB; ++b)
-#pragma unroll
-      for (int c = 0; c < 4; ++c) L.d1[(sb + 16 * b) * LD + ib + 16 * c] *= acc[b][c];
+  gb2 = across_groups(gb2);
+  gw3 = across_groups(gw3);
+  gb3 = across_groups(gb3);
+  loss = across_groups(loss);
+  if (g == 0) {
+    out[OFF_B2 + unit] = gb2;
+    out[OFF_W3 + unit] = gw3;
   }
-  __syncthreads();
-  // dW1[j][k] = sum_s dz1[s][j] x[s][k]
-  for (int o = tid; o < NH * NIN; o += NT) {
-    const int j = o / NIN, k = o - j * NIN;
-    float acc = 0.0f;
-    for (int s = 0; s < TS; ++s) acc = fmaf(L.d1[s * LD + j], L.x[s * NIN + k], acc);
-    g[OFF_W1 + o] = acc;
-  }
-  // biases, W3, and the loss partial
-  if (tid < NH) {
-    float a1 = 0.0f, a2 = 0.0f, a3 = 0.0f;
-    for (int s = 0; s < TS; ++s) {
-      a1 += L.d1[s * LD + tid];
-      a2 += L.d2[s * LD + tid];
-      a3 = fmaf(L.dy[s], L.h2[s * LD + tid], a3);
-    }
-    g[OFF_B1 + tid] = a1;
-    g[OFF_B2 + tid] = a2;
-    g[OFF_W3 + tid] = a3;
-  } else if (tid == NH) {
-    float a = 0.0f, l = 0.0f;
-    for (int s = 0; s < TS; ++s) {
-      a += L.dy[s];
-      l += L.lossv[s];
-    }
-    g[OFF_B3] = a;
-    lossp[blockIdx.x] = l;
+  if (threadIdx.x == 0) {
+    out[OFF_B3] = gb3;
+    lossp[blockIdx.x] = loss;
   }
 }
 
-// grad[p] = sum over blocks (in block order) of the partials; loss = sum of loss partials / count
-__global__ void k_mlp_reduce(const float* __restrict__ part, const float* __restrict__ lossp, int nblk, int count,
-                             float* __restrict__ grad, float* __restrict__ loss) {
-  const int p = blockIdx.x * blockDim.x + threadIdx.x;
+// grad[p] = sum over blocks of the partials, a quarter of them per wave and the quarters in order; loss =
+// sum of loss partials / count.  Both also to the caller's arrays where it gave any (two copies
+// of their own took as long as this kernel).
+constexpr int kReduceParams = 64;
+__global__ void __launch_bounds__(256) k_mlp_reduce(const float* __restrict__ part, const float* __restrict__ lossp,
+                                                    int nblk, int count, float* __restrict__ grad,
+                                                    float* __restrict__ loss, float* __restrict__ grad_out,
+                                                    float* __restrict__ loss_out) {
+  __shared__ float sum[4][kReduceParams];
+  const int k = threadIdx.x % kReduceParams, wave = threadIdx.x / kReduceParams;
+  const int p = blockIdx.x * kReduceParams + k;
+  const int per = (nblk + 3) / 4, lo = min(nblk, wave * per), hi = min(nblk, lo + per);
+  float a = 0.0f;
   if (p < NPARAM) {
-    float a = 0.0f;
-    for (int b = 0; b < nblk; ++b) a += part[(size_t)b * NPARAM + p];
-    grad[p] = a;
+#pragma unroll 8
+    for (int b = lo; b < hi; ++b) a += part[(size_t)b * NPARAM + p];
   } else if (p == NPARAM) {
-    float l = 0.0f;
-    for (int b = 0; b < nblk; ++b) l += lossp[b];
-    *loss = l / (float)count;
+    for (int b = lo; b < hi; ++b) a += lossp[b];
+  }
+  sum[wave][k] = a;
+  __syncthreads();
+  if (wave != 0 || p > NPARAM) return;
+  a = ((sum[0][k] + sum[1][k]) + sum[2][k]) + sum[3][k];
+  if (p < NPARAM) {
+    grad[p] = a;
+    if (grad_out) grad_out[p] = a;
+  } else {
+    a /= (float)count;
+    *loss = a;
+    if (loss_out) *loss_out = a;
   }
 }
 
@@ -335,10 +399,12 @@ void free_mlp(psatd_mlp* p) {
 
 int nblocks(int n, int per) { return (n + per - 1) / per; }
 
-void enqueue_grad(psatd_mlp* p, const float* X, const float* t, int n, const int* idx, int count, hipStream_t s) {
-  const int nb = nblocks(count, TS);
+void enqueue_grad(psatd_mlp* p, const float* X, const float* t, int n, const int* idx, int count, float* grad,
+                  float* loss, hipStream_t s) {
+  const int nb = std::min(nblocks(count, TS), kGradBlocks);
   k_mlp_grad<<<nb, NT, 0, s>>>(p->wbf, X, t, n, idx, count, p->part, p->lossp, p->nm);
-  k_mlp_reduce<<<nblocks(NPARAM + 1, 256), 256, 0, s>>>(p->part, p->lossp, nb, count, p->grad, p->loss);
+  k_mlp_reduce<<<nblocks(NPARAM + 1, kReduceParams), 256, 0, s>>>(p->part, p->lossp, nb, count, p->grad, p->loss, grad,
+                                                                  loss);
 }
 
 void enqueue_adam(psatd_mlp* p, float lr, float beta1, float beta2, float eps, hipStream_t s) {
@@ -377,7 +443,7 @@ int psatd_mlp_create(const float* init, const float* in_mean, const float* in_sc
   p->nm.out_mean = out_mean;
   p->nm.out_scale = out_scale;
   const size_t pb = sizeof(float) * NPARAM;
-  const int nb = nblocks(max_batch, TS);
+  const int nb = std::min(nblocks(max_batch, TS), kGradBlocks);
   if (hipMalloc(&p->master, pb) != hipSuccess || hipMalloc(&p->wbf, sizeof(uint16_t) * NPARAM) != hipSuccess ||
       hipMalloc(&p->m, pb) != hipSuccess || hipMalloc(&p->v, pb) != hipSuccess ||
       hipMalloc(&p->grad, pb) != hipSuccess || hipMalloc(&p->loss, sizeof(float)) != hipSuccess ||
@@ -421,7 +487,7 @@ int psatd_mlp_predict(const psatd_mlp* p, const float* X, int n, float* y, void*
   if (!p || (n > 0 && (!X || !y))) return report_error(PSATD_EINVAL, "psatd_mlp_predict: NULL argument");
   if (n < 0) return report_error(PSATD_EINVAL, "psatd_mlp_predict: n = %d", n);
   if (n == 0) return PSATD_OK;
-  k_mlp_forward<<<nblocks(n, TS), NT, 0, (hipStream_t)stream>>>(p->wbf, X, n, y, p->nm);
+  k_mlp_forward<<<std::min(nblocks(n, TS), kForwardBlocks), NT, 0, (hipStream_t)stream>>>(p->wbf, X, n, y, p->nm);
   return hip_fail("psatd_mlp_predict");
 }
 
@@ -431,9 +497,7 @@ int psatd_mlp_grad(psatd_mlp* p, const float* X, const float* t, int n, const in
   if (n < 1 || batch < 1 || batch > p->max_batch || (!idx && batch > n))
     return report_error(PSATD_EINVAL, "psatd_mlp_grad: n = %d, batch = %d (max %d)", n, batch, p->max_batch);
   hipStream_t s = (hipStream_t)stream;
-  enqueue_grad(p, X, t, n, idx, batch, s);
-  if (grad) (void)hipMemcpyAsync(grad, p->grad, sizeof(float) * NPARAM, hipMemcpyDeviceToDevice, s);
-  if (loss) (void)hipMemcpyAsync(loss, p->loss, sizeof(float), hipMemcpyDeviceToDevice, s);
+  enqueue_grad(p, X, t, n, idx, batch, grad, loss, s);
   return hip_fail("psatd_mlp_grad");
 }
 
@@ -453,8 +517,8 @@ int psatd_mlp_train(psatd_mlp* p, const float* X, const float* t, int n, const i
   if (!adam_args_ok(lr, beta1, beta2, eps)) return report_error(PSATD_EINVAL, "psatd_mlp_train: bad hyperparameters");
   hipStream_t s = (hipStream_t)stream;
   for (int k = 0; k < nsteps; ++k) {
-    enqueue_grad(p, X, t, n, idx ? idx + (size_t)k * batch : nullptr, batch, s);
-    if (loss_hist) (void)hipMemcpyAsync(loss_hist + k, p->loss, sizeof(float), hipMemcpyDeviceToDevice, s);
+    enqueue_grad(p, X, t, n, idx ? idx + (size_t)k * batch : nullptr, batch, nullptr,
+                 loss_hist ? loss_hist + k : nullptr, s);
     enqueue_adam(p, lr, beta1, beta2, eps, s);
   }
   return hip_fail("psatd_mlp_train");

@@ -152,3 +152,26 @@ def test_label_matches_oracle_local_vs_global(lib):
             ref = omlp.truncation_error(loc[0:6], glo[0:6])
             assert ref > -12.0  # a real truncation error, far above round-off
             assert abs(e - ref) <= 1e-6 * abs(ref) + 1e-9, (ng, k, e, ref)
+
+
+@pytest.mark.parametrize("n,batch", [(32768 + 17, 8192 + 15), (17, 16), (33, 33)])
+def test_blocks_of_several_tiles_match_oracle(lib, n, batch):
+    """More tiles than blocks (prediction and gradient), whole tiles and a tile of one sample."""
+    import torch
+
+    net = _make(lib, seed=12, max_batch=batch)
+    X, t = _inputs(13, n)
+    Xg, tg = torch.as_tensor(X, device="cuda"), torch.as_tensor(t, device="cuda")
+    _, wbf = net.params()
+    y = net.predict(Xg).cpu().numpy().astype(np.float64)
+    ref, _ = omlp.forward(wbf.astype(np.float64), _std(X))
+    ref = OUT_MEAN + OUT_SCALE * ref
+    assert np.max(np.abs(y - ref)) <= 1e-5 * max(1.0, np.abs(ref).max())
+    idx = np.random.default_rng(14).integers(0, n, size=batch).astype(np.int32)
+    g, loss = net.grad(Xg, tg, torch.as_tensor(idx, device="cuda"), batch=batch)
+    L, gref = omlp.loss_and_grad(wbf.astype(np.float64), _std(X[idx]), (t[idx].astype(np.float64) - OUT_MEAN) / OUT_SCALE)
+    assert abs(float(loss.cpu()) - L) <= 1e-5 * L
+    got, exp = _tensor_groups(g.cpu().numpy()), _tensor_groups(gref)
+    for k in got:
+        assert np.linalg.norm(got[k] - exp[k]) <= 1e-5 * np.linalg.norm(exp[k]), k
+    net.close()
