@@ -48,6 +48,8 @@ struct XFwdParams {
   int ld_drow, ld_dcol;  // block stride over (complex line, x) = divmod(threads, NX)
   int wr_drow, wr_dcol;  // block stride over (kx, complex line) = divmod(threads, ty / 2)
   int pnl, pnl_sh, pthreads;  // pair kernels: complex lines per tile (a power of two), its shift, block size
+  int pml;               // PML, pair kernels: fields 0..5 are src[f] + add[f], the two split parts
+  const T* add[6];
   PairFFT<T> pair;
   LineFFT<T> fft;
 };
@@ -133,6 +135,8 @@ struct XInvParams {
   int nthreads;          // block size the tile was fitted for (kXInvThreads, or kLineThreads
                          // when a line's butterflies exceed the smaller block)
   int pnl, pnl_sh, pthreads;  // pair kernels: complex lines per tile (a power of two), its shift, block size
+  int pml;               // PML, pair kernels, box: dst = (dst + value) * damp[(f % 3 + pml) % 3], pml = split set 1 or 2
+  const T* damp[3];      // per axis, one factor per coordinate of the box
   PairFFT<T> pair;
   LineFFT<T> fft;
 };

@@ -38,7 +38,9 @@ __device__ __forceinline__ Tw<T>* tables_after(cx<T>* lds, int lines, const Pair
 }
 
 // ------------------------------------------------------------------ P1
-template <int CLASS, bool BATCH, typename T, typename Src>
+// PML: a full field is the sum of its two split parts, added as they are loaded (the sources have
+// one array: an empty buffer reads as zero).
+template <int CLASS, bool BATCH, bool PML, typename T, typename Src>
 __device__ __forceinline__ void pair_xfwd_body(const Src& S) {
   cx<T>* lds = lds_base<T>();
   const int nth = blockDim.x;
@@ -80,13 +82,21 @@ __device__ __forceinline__ void pair_xfwd_body(const Src& S) {
       const uint32_t oa = ya < NY ? (uint32_t)((zrow + ra) * rowlen) : kOOB;
       const uint32_t ob = ya + 1 < NY ? (uint32_t)((zrow + rb) * rowlen) : kOOB;
       const rsrc_t src = make_rsrc(p.src[f], p.src_bytes);
+      rsrc_t add = src;
+      if constexpr (PML) add = make_rsrc(p.add[f < 6 ? f : 0], f < 6 ? p.src_bytes : 0u);
+      auto load = [&](uint32_t i) PSATD_INLINE {
+        if constexpr (PML)
+          return gm<T>::ld(src, i) + gm<T>::ld(add, i);
+        else
+          return gm<T>::ld(src, i);
+      };
       const int* xo = xoff + j;
       const int cb = fdiv(tid, P.fa), kb = tid - cb * RA;
       if constexpr (chirp_class(CLASS)) {
         chirp_stage_a<CLASS, -1, false>(lds, P, c, j, active, [&](auto, int t) PSATD_INLINE {
           const bool in = j + RB * t < N;
           const uint32_t xs = in ? (uint32_t)xo[RB * t] : 0u;
-          return cx<T>{gm<T>::ld(src, in ? oa + xs : kOOB), gm<T>::ld(src, in ? ob + xs : kOOB)};
+          return cx<T>{load(in ? oa + xs : kOOB), load(in ? ob + xs : kOOB)};
         });
         __syncthreads();
         chirp_stage_b<CLASS, -1>(lds, tw, P, cb, kb, cb < nc);
@@ -97,7 +107,7 @@ __device__ __forceinline__ void pair_xfwd_body(const Src& S) {
       } else {
         pair_stage_a<CLASS, -1, false>(lds, P, c, j, active, [&](auto, int t) PSATD_INLINE {
           const uint32_t xs = (uint32_t)xo[RB * t];
-          return cx<T>{gm<T>::ld(src, oa + xs), gm<T>::ld(src, ob + xs)};
+          return cx<T>{load(oa + xs), load(ob + xs)};
         });
         __syncthreads();
         pair_stage_b<CLASS, -1, true>(lds, tw, P, cb, kb, cb < nc, [&](int t, cx<T> v) PSATD_INLINE {
@@ -336,7 +346,10 @@ __device__ __forceinline__ void pair_zpush_body(const Src& S) {
 // loads: point i is X + i Y of bin i up to N/2 and conj X + i conj Y of bin N - i above
 // (each bin is read twice, the second time from the caches, which costs less than the LDS
 // round trip and the barrier of a rebuilt line).
-template <int CLASS, bool BATCH, typename T, typename Src>
+// PML: the increment of one split set goes straight into its parts, damped (kPmlRows values of each row
+// in flight: a read per store would leave the stores waiting for one read each).
+constexpr int kPmlRows = 4;
+template <int CLASS, bool BATCH, bool PML, typename T, typename Src>
 __device__ __forceinline__ void pair_xinv_body(const Src& S) {
   cx<T>* lds = lds_base<T>();
   const int nth = blockDim.x;
@@ -401,7 +414,32 @@ __device__ __forceinline__ void pair_xinv_body(const Src& S) {
     __syncthreads();
     // the two real rows of each line (box, or interior of G1), written along x so that
     // a wave's stores cover whole rows
-    {
+    if constexpr (PML) {
+      const rsrc_t dst = make_rsrc(p.dst[f], p.dst_bytes);
+      const int f3 = f < 3 ? f : f - 3, axis = f3 + p.pml < 3 ? f3 + p.pml : f3 + p.pml - 3;
+      const T* dm = p.damp[axis];
+      for (int e0 = tid; e0 < nc * N; e0 += kPmlRows * nth) {
+        uint32_t ia[kPmlRows], ib[kPmlRows];
+        cx<T> val[kPmlRows], part[kPmlRows], damp[kPmlRows];
+#pragma unroll
+        for (int u = 0; u < kPmlRows; ++u) {
+          const int e = min(e0 + u * nth, nc * N - 1), c = fdiv(e, p.fd_nx), n = e - c * N;
+          const bool in = e0 + u * nth < nc * N;
+          const int ya = ybase + 2 * c;
+          ia[u] = in && ya < NY ? (uint32_t)((z * NY + ya) * N + n) : kOOB;
+          ib[u] = in && ya + 1 < NY ? (uint32_t)((z * NY + ya + 1) * N + n) : kOOB;
+          part[u] = {gm<T>::ld(dst, ia[u]), gm<T>::ld(dst, ib[u])};
+          damp[u] = {dm[axis == 0 ? n : axis == 1 ? min(ya, NY - 1) : z],
+                     dm[axis == 0 ? n : axis == 1 ? min(ya + 1, NY - 1) : z]};
+          val[u] = lds[c * P.ld + n];
+        }
+#pragma unroll
+        for (int u = 0; u < kPmlRows; ++u) {
+          gm<T>::template st<kXStore<T>>(dst, ia[u], (part[u].re + val[u].re) * damp[u].re);
+          gm<T>::template st<kXStore<T>>(dst, ib[u], (part[u].im + val[u].im) * damp[u].im);
+        }
+      }
+    } else {
       const rsrc_t dst = make_rsrc(p.dst[f], p.dst_bytes);
       const int zrow = p.scatter ? fmod_i(p.oz + z - p.gz, p.fd_GZ) * p.GY : z * NY;
       const int rowlen = p.scatter ? p.GX : N;
@@ -450,13 +488,13 @@ constexpr int kPairThreads = pair_threads_max(sizeof(T) == 8, CLASS, false);
 #define PSATD_PAIR_ATTR(T, C, W) \
   __global__ void __launch_bounds__((kPairThreads<T, C>)) __attribute__((amdgpu_waves_per_eu(W<T, C>)))
 
-template <typename T, int C>
+template <typename T, int C, bool PML>
 PSATD_PAIR_ATTR(T, C, kPairWaves) k_pxfwd(XFwdParams<T>) {
-  pair_xfwd_body<C, false, T>(SingleSrc<XFwdParams<T>>{});
+  pair_xfwd_body<C, false, PML, T>(SingleSrc<XFwdParams<T>>{});
 }
 template <typename T, int C>
 PSATD_PAIR_ATTR(T, C, kPairWaves) k_pxfwd_b(BatchArgs<XFwdParams<T>> a) {
-  pair_xfwd_body<C, true, T>(BatchSrc<XFwdParams<T>>{a});
+  pair_xfwd_body<C, true, false, T>(BatchSrc<XFwdParams<T>>{a});
 }
 template <int S, typename T, int C>
 PSATD_PAIR_ATTR(T, C, kPairWavesY) k_pypass(YPassParams<T>) {
@@ -474,13 +512,13 @@ template <typename T, int C>
 __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(kPairWavesZ<T, C>))) k_pzpush_b(BatchArgs<ZPushParams<T>> a) {
   pair_zpush_body<C, true, false, T>(BatchSrc<ZPushParams<T>>{a});
 }
-template <typename T, int C>
+template <typename T, int C, bool PML>
 PSATD_PAIR_ATTR(T, C, kPairWavesXInv) k_pxinv(XInvParams<T>) {
-  pair_xinv_body<C, false, T>(SingleSrc<XInvParams<T>>{});
+  pair_xinv_body<C, false, PML, T>(SingleSrc<XInvParams<T>>{});
 }
 template <typename T, int C>
 PSATD_PAIR_ATTR(T, C, kPairWavesXInv) k_pxinv_b(BatchArgs<XInvParams<T>> a) {
-  pair_xinv_body<C, true, T>(BatchSrc<XInvParams<T>>{a});
+  pair_xinv_body<C, true, false, T>(BatchSrc<XInvParams<T>>{a});
 }
 
 // LDS of a pair block: its lines, the stage B twiddles, and P1's column table.
@@ -494,7 +532,11 @@ size_t pair_lds(const PairFFT<T>& P, int lines, int ints) {
 // ------------------------------------------------------------------ launchers
 template <typename T, int C>
 void launch_pair_xfwd_c(const XFwdParams<T>& p, hipStream_t s) {
-  launch_persistent(k_pxfwd<T, C>, p, p.pthreads, pair_lds(p.pair, p.pnl, p.NX), p.ntiles, s);
+  const size_t lds = pair_lds(p.pair, p.pnl, p.NX);
+  if (p.pml)
+    launch_persistent(k_pxfwd<T, C, true>, p, p.pthreads, lds, p.ntiles, s);
+  else
+    launch_persistent(k_pxfwd<T, C, false>, p, p.pthreads, lds, p.ntiles, s);
 }
 template <typename T, int C>
 void launch_pair_ypass_c(const YPassParams<T>& p, int inverse, hipStream_t s) {
@@ -514,7 +556,11 @@ void launch_pair_zpush_c(const ZPushParams<T>& p, hipStream_t s) {
 }
 template <typename T, int C>
 void launch_pair_xinv_c(const XInvParams<T>& p, hipStream_t s) {
-  launch_persistent(k_pxinv<T, C>, p, p.pthreads, pair_lds(p.pair, p.pnl, 0), p.ntiles, s);
+  const size_t lds = pair_lds(p.pair, p.pnl, 0);
+  if (p.pml)
+    launch_persistent(k_pxinv<T, C, true>, p, p.pthreads, lds, p.ntiles, s);
+  else
+    launch_persistent(k_pxinv<T, C, false>, p, p.pthreads, lds, p.ntiles, s);
 }
 template <typename T, int C>
 void launch_pair_xfwd_batch(const BatchArgs<XFwdParams<T>>& a, int threads, size_t lds, hipStream_t s) {

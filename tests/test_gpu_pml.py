@@ -138,3 +138,10 @@ def test_outgoing_pulse_is_absorbed(lib, precision):
     tol = 1e-10 if precision == "fp64" else 2e-3  # 640 FP32 steps
     assert np.abs(got - ref).max() <= tol
     plan.close()
+
+
+@pytest.mark.parametrize("precision", ["fp64", "fp32"])
+@pytest.mark.parametrize("interior,widths", [((1056, 7, 6), (8, 1, 1)), ((311, 9, 6), (5, 2, 0)), ((6, 1, 8), (1, 0, 2))])
+def test_parts_summed_and_damped_in_the_x_passes(lib, precision, interior, widths):
+    """Large direct and chirp-z radices along x, an odd row at the end of a tile, a single row."""
+    test_pml_steps_match_oracle(lib, precision, interior, 0, 8, widths)
