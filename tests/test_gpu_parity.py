@@ -187,6 +187,31 @@ def test_guard_fill_and_merge_are_exact(lib, precision):
     plan.close()
 
 
+@pytest.mark.parametrize("precision", ["fp64", "fp32"])
+@pytest.mark.parametrize("nfields,interior,ng,gshape", [(11, (130, 3, 2), 1, (5, 4, 131)), (5, (1, 2, 3), 0, (3, 2, 1)),
+                                                        (6, (61, 5, 3), 1, (4, 6, 64)), (1, (64, 1, 1), 2, (2, 3, 64))])
+def test_guard_rows_of_any_width_and_number_of_arrays(lib, precision, nfields, interior, ng, gshape):
+    """Rows of 1, 63 to 68 and 132 cells, groups of four arrays with a remainder, wraps in x."""
+    import torch
+
+    origin = (gshape[2] - 1, gshape[1] - 1, 0)
+    plan = lib.Plan(*interior, nguard=ng, order=4, precision=precision)
+    g = _to_gpu(synth.random_fields(synth.rng_for(104, nfields), gshape, nfields=nfields), plan.dtype)
+    box = torch.zeros((nfields,) + plan.box_shape, dtype=plan.dtype, device="cuda")
+    plan.guard_fill(list(g), list(box), origin)
+    idx = [torch.as_tensor((origin[a] - ng + np.arange(plan.box_shape[2 - a])) % gshape[2 - a], device="cuda")
+           for a in range(3)]
+    assert torch.equal(box, g[:, idx[2]][:, :, idx[1]][:, :, :, idx[0]])
+    out, box = torch.zeros_like(g), box + 1
+    plan.guard_merge(list(box), list(out), origin, mode=0)
+    ref = torch.zeros_like(g)
+    zi, yi, xi = (idx[2 - k][ng:ng + interior[2 - k]] for k in range(3))
+    ref[:, zi[:, None, None], yi[None, :, None], xi[None, None, :]] = box[:, ng:ng + len(zi), ng:ng + len(yi),
+                                                                        ng:ng + len(xi)]
+    assert torch.equal(out, ref)
+    plan.close()
+
+
 def test_config1_ten_steps_fp64(lib):
     """32^3 periodic grid, infinite order, dt = dx/2, 10 steps (plane waves + Gaussian current)."""
     import torch
