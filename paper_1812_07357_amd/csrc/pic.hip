@@ -183,7 +183,7 @@ __device__ __forceinline__ T gather_at(const T* __restrict__ f, const Points<K, 
 // the lines moved (7 TB/s out of the 256 MB cache).  Side by side its stencil is 16 rows of
 // 96 bytes.  33.5 M cubic particles in random order on 256x128x128, FP32: 61.1 -> 15.9 ms
 // (linear 14.8 -> 3.5); 67 M linear ones in cell order on 512x256x256 1.63 -> 1.59 ms, 44
-// steps later 10.8 -> 4.3 ms; FP64 cubic 33.5 -> 28.9 ms.
+// steps later 10.8 -> 4.3 ms; 16.8 M cubic ones in FP64 33.6 -> 11.6 ms.
 template <typename T>
 struct Six {
   const T* f[6];
@@ -221,21 +221,23 @@ __global__ void __launch_bounds__(kPicThreads) k_interleave(Six<T> a, T* __restr
 }
 
 // All six components at a particle from the interleaved cells: a row of K + 1 points is one run of
-// 6 (K + 1) values.
+// 6 (K + 1) values.  Above degree 1 one plane of rows is in flight at a time (a loop that is not
+// unrolled): the loads of all planes together took 424 registers at degree 3 and left one wavefront
+// per SIMD (67 M particles in cell order, FP32: 10.4 ms against 5.3; 16.8 M in random order, FP64: 28.5 against 11.6).
 template <int K, typename T>
-__device__ __forceinline__ void gather_six(T* eb, const T* __restrict__ cells, const Points<K, T>& g) {
+__device__ __forceinline__ void gather_six(T* eb, const T* __restrict__ cells, Points<K, T>& g) {
   // 16-byte loads; FP32 rows of three points are 18 values, in 8-byte loads
   constexpr int V = sizeof(T) == 8 || K == 2 ? 2 : 4, NV = 6 * (K + 1) / V;
   typedef T vec_t __attribute__((ext_vector_type(V), aligned(alignof(T))));
 #pragma unroll
   for (int k = 0; k < 6; ++k) eb[k] = 0;
   const bool run = g.xs[K] == g.xs[0] + K;
-#pragma unroll
-  for (int cz = 0; cz <= K; ++cz)
+#pragma unroll(K == 1 ? 2 : 1)
+  for (int cz = 0; cz <= K; ++cz) {
 #pragma unroll
     for (int cy = 0; cy <= K; ++cy) {
-      const T wyz = g.wy[cy] * g.wz[cz];
-      const long long row = (long long)g.zs[cz] + g.ys[cy];
+      const T wyz = g.wy[cy] * g.wz[0];
+      const long long row = (long long)g.zs[0] + g.ys[cy];
       T v[6 * (K + 1)];
       if (run) {
         const vec_t* p = reinterpret_cast<const vec_t*>(cells + (row + g.xs[0]) * 6);
@@ -258,6 +260,13 @@ __device__ __forceinline__ void gather_six(T* eb, const T* __restrict__ cells, c
         for (int k = 0; k < 6; ++k) eb[k] += v[cx * 6 + k] * w;
       }
     }
+    // the next plane moves to the front (no index that varies at run time into the registers)
+#pragma unroll
+    for (int c = 0; c < K; ++c) {
+      g.wz[c] = g.wz[c + 1];
+      g.zs[c] = g.zs[c + 1];
+    }
+  }
 }
 
 template <typename T>
@@ -273,7 +282,7 @@ struct PushPtrs {
 // STAG: staggered grid (each component at its own half-cell offsets); otherwise the six
 // components share one set of points and weights.  SIX: from interleaved cells.
 template <typename T, bool STAG, int K, bool SIX>
-__global__ void __launch_bounds__(kPicThreads) k_pic_push(PicArgs<T> a, PushPtrs<T> p) {
+__global__ void __launch_bounds__(kPicThreads) __attribute__((amdgpu_waves_per_eu(2))) k_pic_push(PicArgs<T> a, PushPtrs<T> p) {
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= a.n) return;
   // the particle arrays stream through once (non-temporal), which leaves the caches to the
