@@ -864,8 +864,9 @@ struct psatd_pic {
       (void)hipGetLastError();
       return false;
     }
-    if (!cells_used || cells_stream == s) return true;
-    const hipError_t e = hipEventQuery(cells_done);
+    if (!cells_used) return true;
+    // (the same handle may be a new stream, whose predecessor still runs: ordered by the event)
+    const hipError_t e = cells_stream == s ? hipStreamWaitEvent(s, cells_done, 0) : hipEventQuery(cells_done);
     if (e != hipSuccess) (void)hipGetLastError();
     return e == hipSuccess;
   }
