@@ -583,6 +583,20 @@ int scratch_slot(ScratchSlot** out) {
   return PSATD_OK;
 }
 
+// Tables of the Stockham kernels of an axis: what is not there yet is allocated, then filled on the
+// null stream (the caller synchronises).
+int alloc_line_tables(psatd_plan* p, Axis* a) {
+  const size_t tws = p->fp64 ? sizeof(Tw<double>) : sizeof(Tw<float>);
+  int rc = a->tw ? PSATD_OK : dalloc(p, &a->tw, tws * a->sch.n);
+  if (!rc && a->blue && !a->chirp) rc = dalloc(p, &a->chirp, tws * a->n);
+  if (!rc && a->blue && !a->filt) rc = dalloc(p, &a->filt, tws * a->sch.n);
+  return rc;
+}
+void fill_line_tables(const psatd_plan* p, const Axis* a) {
+  launch_twiddles(a->tw, a->sch, p->fp64, nullptr);
+  if (a->blue) launch_bluestein(a->chirp, a->n, a->filt, a->n, a->sch.n, p->fp64, nullptr);
+}
+
 // Layout B strides of plan p for `fields` fields: between the fields of a column, between columns.
 i64 b_field_stride(const psatd_plan* p) { return p->interleaved ? (i64)p->NZ : (i64)p->npts; }
 i64 b_column_stride(const psatd_plan* p, int fields) { return p->interleaved ? (i64)fields * p->NZ : (i64)p->NZ; }
@@ -657,8 +671,7 @@ int build_plan(const psatd_plan_desc* d, psatd_plan** out, bool large = true) {
       rc = dalloc(p, &q.tw, tws * 2 * q.m);
       if (!rc && q.blue && !(rc = dalloc(p, &q.chirp, tws * q.m))) rc = dalloc(p, &q.filt, tws * q.m);
     } else {
-      rc = dalloc(p, &a->tw, tws * a->sch.n);
-      if (!rc && a->blue && !(rc = dalloc(p, &a->chirp, tws * a->n))) rc = dalloc(p, &a->filt, tws * a->sch.n);
+      rc = alloc_line_tables(p, a);
     }
     if (rc) {
       std::string msg = g_err;
@@ -684,8 +697,7 @@ int build_plan(const psatd_plan_desc* d, psatd_plan** out, bool large = true) {
       launch_pair_twiddles(q.tw, q.ra, q.rb, p->fp64, s);
       if (q.blue) launch_bluestein(q.chirp, q.m, q.filt, q.n, q.m, p->fp64, s);
     } else {
-      launch_twiddles(a->tw, a->sch, p->fp64, s);
-      if (a->blue) launch_bluestein(a->chirp, a->n, a->filt, a->n, a->sch.n, p->fp64, s);
+      fill_line_tables(p, a);
     }
   }
   const int stag = (d->flags & PSATD_FLAG_STAGGERED) ? 1 : 0;
@@ -933,7 +945,8 @@ void build_step(psatd_plan* p, const StepIO& io, StepParams<T>& sp) {
   z3.inv_n = T(1.0 / ((double)NX * NY * NZ));
   int nc = p->zcols;
   if (p->pair[2].ra) {
-    // PML: twelve lines per column, maybe fewer columns (or none: the Stockham kernel)
+    // PML: twelve lines per column, maybe fewer columns (or none: the Stockham kernel, whose
+    // tables psatd_pml_set then made)
     const int pc = pair_tile(p->pair[2], 2, p->fp64 != 0, fields);
     if (pc > 0) {
       z3.pair = pair_fft<T>(p->pair[2], 2, 0);
@@ -1050,8 +1063,22 @@ void launch_p5(const XInvParams<T>& p, int cls, hipStream_t s) {
   with_class(cls, [&](auto c) { launch_pair_xinv_c<T, decltype(c)::value>(p, s); });
 }
 
+// Whether every pass has the tables of the kernel that it is about to run.
+template <typename T>
+int check_tables(const psatd_plan* p, const StepParams<T>& sp) {
+  auto ready = [&](const auto& q, int axis) {
+    if (q.pair.ra) return q.pair.tw && (!p->pair[axis].blue || (q.pair.chirp && q.pair.filt));
+    return q.fft.tw && (!q.fft.blue || (q.fft.chirp && q.fft.filt));
+  };
+  if (ready(sp.x1, 0) && ready(sp.y2, 1) && ready(sp.z3, 2) && ready(sp.y4, 1) && ready(sp.x5, 0)) return PSATD_OK;
+  return fail(PSATD_ESTATE, "box %dx%dx%d: a pass has no tables for its kernel", p->NX, p->NY, p->NZ);
+}
+
 template <typename T>
 int run_step(psatd_plan* p, const StepIO& io, hipStream_t s, bool allow_timing = true) {
+  StepParams<T> sp;
+  build_step<T>(p, io, sp);
+  if (int rc = check_tables(p, sp)) return rc;
   Marks mk;
   mk.s = s;
   if (p->timing && allow_timing) {
@@ -1061,8 +1088,6 @@ int run_step(psatd_plan* p, const StepIO& io, hipStream_t s, bool allow_timing =
     p->events.push_back(set);
     mk.set = &p->events.back();
   }
-  StepParams<T> sp;
-  build_step<T>(p, io, sp);
   mk.mark(0);
   launch_p1<T>(sp.x1, p->pair[0].cls, s);
   mk.mark(1);
@@ -1087,6 +1112,7 @@ template <typename T>
 int run_pml(psatd_plan* p, const StepIO& io, void* const* parts, hipStream_t s) {
   StepParams<T> sp;
   build_step<T>(p, io, sp);
+  if (int rc = check_tables(p, sp)) return rc;
   const bool fused = p->pair[0].ra != 0;
   if (fused) {
     sp.x1.pml = 1;
@@ -1411,8 +1437,10 @@ void tune_pair(psatd_plan* p, int a, hipStream_t s) {
   std::snprintf(key, sizeof key, "%s|%c|n=%d|m=%d|other=%dx%d", p->fp64 ? "fp64" : "fp32", "xyz"[a], base.n, base.m,
                 lens[(a + 1) % 3], lens[(a + 2) % 3]);
   std::vector<PairAxis> cands;
+  // (with absorbing layers set, a z pair has to hold twelve lines unless the Stockham tables are there too)
+  const int fields = a == 2 && p->pml_ready && !p->az.tw ? 12 : 11;
   for (const PairAxis& c : ranked_pairs(base.n, p->large_radices))
-    if (c.m == base.m && pair_tile(c, a, p->fp64 != 0, 11) > 0) cands.push_back(c);
+    if (c.m == base.m && pair_tile(c, a, p->fp64 != 0, fields) > 0) cands.push_back(c);
   auto use = [&](PairAxis c) {
     c.tw = base.tw;
     c.chirp = base.chirp;
@@ -1928,6 +1956,14 @@ int psatd_pml_set(psatd_plan* p, const int width[3], double sigma_max, double po
   const size_t rs = p->rsize;
   if ((size_t)12 * lds_line(p->az.sch.n) * 2 * rs > lds_limit())
     return fail(PSATD_EUNSUPPORTED, "psatd_pml_set: twelve z lines of %d points do not fit the LDS", p->az.sch.n);
+  // A z pair that holds the step's eleven lines but not twelve (FP64, 768 to 800 points): the z pass
+  // with the split increments runs on the Stockham kernel.
+  if (p->pair[2].ra && pair_tile(p->pair[2], 2, p->fp64 != 0, 12) < 1) {
+    if (int rc = alloc_line_tables(p, &p->az)) return rc;
+    fill_line_tables(p, &p->az);
+    if (int rc = check_hip("psatd_pml_set")) return rc;
+    if (hipDeviceSynchronize() != hipSuccess) return check_hip("psatd_pml_set");
+  }
   if (!p->pml_ready) {
     if (int rc = dalloc(p, &p->pml_wsB, (size_t)12 * p->npts * 2 * rs)) return rc;
     for (int a = 0; a < 3; ++a)

@@ -145,3 +145,10 @@ def test_outgoing_pulse_is_absorbed(lib, precision):
 def test_parts_summed_and_damped_in_the_x_passes(lib, precision, interior, widths):
     """Large direct and chirp-z radices along x, an odd row at the end of a tile, a single row."""
     test_pml_steps_match_oracle(lib, precision, interior, 0, 8, widths)
+
+
+@pytest.mark.parametrize("interior,widths", [((6, 5, 800), (1, 1, 60)), ((5, 4, 380), (0, 1, 30)), ((4, 6, 344), (1, 0, 9))])
+def test_z_lines_of_which_eleven_fit_the_lds_but_not_twelve(lib, interior, widths):
+    """FP64 z pairs that the step's z pass takes and the one with the split increments cannot: direct
+    (800) and chirp-z (380 and 344: 32 * 24 padded points)."""
+    test_pml_steps_match_oracle(lib, "fp64", interior, 0, 8, widths)
