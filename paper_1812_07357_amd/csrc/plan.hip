@@ -1236,13 +1236,31 @@ std::map<std::string, TuneEntry>& tune_cache() {
 // under another version are discarded.
 constexpr int kTuneSchema = 3;
 
+// The two kinds of kernels have radices, tiles and cache entries of their own: the key of an entry
+// for the pair kernels ends with the pairs it was chosen from (all, or the small radices that
+// batches run).
+const char* pair_key(bool large) { return large ? "|pairs=all" : "|pairs=small"; }
+bool is_pair_key(const std::string& key) { return key.find("|pairs=") != std::string::npos; }
+
 bool compiled_radix(int r) {
   for (int k : kRadix)
     if (k == r) return true;
-  return in_list(r, radices<0>::a{}) || in_list(r, radices<1>::a{});
+  return false;
 }
 
-// A radix sequence is usable for a transform of length m when its radices are all
+// A sequence of one or two radices is a pair of length m when a class of pair kernels has both.
+template <int C>
+bool class_has(int ra, int rb) {
+  return in_list(ra, typename radices<C>::a{}) && in_list(rb, typename radices<C>::b{});
+}
+bool valid_pair(const std::vector<int>& r, int m) {
+  if (r.empty() || r.size() > 2) return false;
+  const int ra = r[0], rb = r.size() > 1 ? r[1] : 1;
+  return ra * rb == m && ra >= rb &&
+         (class_has<0>(ra, rb) || class_has<1>(ra, rb) || class_has<2>(ra, rb) || class_has<3>(ra, rb));
+}
+
+// A radix sequence is usable for a Stockham transform of length m when its radices are all
 // compiled and multiply to m.
 bool valid_radices(const std::vector<int>& r, int m) {
   if (m < 1 || (int)r.size() > kMaxStages || (m > 1 && r.empty())) return false;
@@ -1355,7 +1373,8 @@ void load_tune_file(const char* path, int* accepted = nullptr, int* rejected = n
       ++bad;
       break;
     }
-    if (current && e.tile > 0 && valid_radices(e.radix, key_length(key))) {
+    const int m = key_length(key);
+    if (current && e.tile > 0 && (is_pair_key(key) ? valid_pair(e.radix, m) : valid_radices(e.radix, m))) {
       tune_cache()[key] = e;
       ++ok;
     } else {
@@ -1434,8 +1453,8 @@ void tune_pair(psatd_plan* p, int a, hipStream_t s) {
   const PairAxis base = p->pair[a];
   const int lens[3] = {p->NX, p->NY, p->NZ};
   char key[160];
-  std::snprintf(key, sizeof key, "%s|%c|n=%d|m=%d|other=%dx%d", p->fp64 ? "fp64" : "fp32", "xyz"[a], base.n, base.m,
-                lens[(a + 1) % 3], lens[(a + 2) % 3]);
+  std::snprintf(key, sizeof key, "%s|%c|n=%d|m=%d|other=%dx%d%s", p->fp64 ? "fp64" : "fp32", "xyz"[a], base.n, base.m,
+                lens[(a + 1) % 3], lens[(a + 2) % 3], pair_key(p->large_radices));
   std::vector<PairAxis> cands;
   // (with absorbing layers set, a z pair has to hold twelve lines unless the Stockham tables are there too)
   const int fields = a == 2 && p->pml_ready && !p->az.tw ? 12 : 11;

@@ -243,3 +243,23 @@ def test_pml_null_arguments(lib):
     assert L.psatd_pml_set(None, w, 1.0, 2.0) == lib.PSATD_EINVAL
     assert L.psatd_pml_step(None, None, None, None) == lib.PSATD_EINVAL
 
+
+
+def test_tune_cache_entries_are_checked_by_the_kernels_they_are_for(lib, tmp_path):
+    """Pair radices are no Stockham stages, and a pair entry names one pair of one class."""
+    rejected = [
+        '    "fp32|x|n=490|m=490|other=8x8": {"radix": [14, 7, 5], "tile": 8}',              # 14: pairs only
+        '    "fp32|x|n=600|m=600|other=8x8": {"radix": [25, 24], "tile": 8}',
+        '    "fp64|y|n=1056|m=1056|other=8x8": {"radix": [33, 32], "tile": 8}',
+        '    "fp32|x|n=490|m=490|other=8x8|pairs=all": {"radix": [14, 7, 5], "tile": 8}',    # three radices
+        '    "fp32|x|n=600|m=600|other=8x8|pairs=all": {"radix": [24, 25], "tile": 8}',      # the larger comes first
+        '    "fp32|x|n=19|m=38|other=8x8|pairs=all": {"radix": [19, 2], "tile": 8}',
+    ]
+    accepted = [
+        '    "fp32|x|n=600|m=600|other=8x8": {"radix": [24, 5, 5], "tile": 8}',
+        '    "fp32|x|n=600|m=600|other=8x8|pairs=all": {"radix": [25, 24], "tile": 8}',
+        '    "fp64|z|n=24|m=24|other=8x8|pairs=small": {"radix": [24], "tile": 8}',
+    ]
+    for i, entry in enumerate(rejected):
+        assert lib.tune_cache_load(_write_cache(tmp_path / f"r{i}.json", entry)) == (0, 1), entry
+    assert lib.tune_cache_load(_write_cache(tmp_path / "a.json", ",\n".join(accepted))) == (3, 0)

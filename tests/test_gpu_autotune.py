@@ -41,3 +41,27 @@ def test_autotuned_plan_matches_oracle_and_cache_roundtrips(lib, tmp_path, preci
     plan.close()
     plan2.close()
     assert os.path.getsize(path) > 0
+
+
+@pytest.mark.parametrize("precision", ["fp32", "fp64"])
+def test_plan_and_batch_autotuned_through_one_cache(lib, tmp_path, precision):
+    """600 points are the pair 25 * 24 in a plan and Stockham stages in a batch: the batch after the plan,
+    through one cache file, still matches the oracle."""
+    import torch
+
+    dims, order, dt = (600, 6, 5), 8, 0.5
+    path = str(tmp_path / "tune.json")
+    dtype = torch.float64 if precision == "fp64" else torch.float32
+    f = synth.random_fields(synth.rng_for(401, 0), dims[::-1])
+    ref = step.box_step(f, 1.0, dt, order)
+    plan = lib.Plan(*dims, nguard=0, order=order, dt=dt, precision=precision)
+    batch = lib.Batch([dict(origin=(0, 0, 0), interior=dims, nguard=0, order=order)], dims, dt=dt, precision=precision)
+    plan.autotune(path)
+    batch.autotune(path)
+    for obj in (plan, batch):
+        g = torch.as_tensor(f, dtype=dtype, device="cuda")
+        obj.push_fields(g) if obj is plan else obj.step(g)
+        torch.cuda.synchronize()
+        err = np.abs(g[0:6].double().cpu().numpy() - ref).max() / np.abs(ref).max()
+        assert err <= (1e-12 if precision == "fp64" else 2e-5), (type(obj).__name__, err)
+        obj.close()

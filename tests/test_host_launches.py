@@ -40,3 +40,8 @@ def _run(exe, *args):
 def test_every_pml_z_pass_has_its_tables(tmp_path):
     """Twelve z lines per column may not fit the LDS where the step's eleven do (FP64)."""
     _run(_build(tmp_path, "pml_z_tables"))
+
+
+def test_plans_and_batches_share_a_tune_cache(tmp_path):
+    """Pair radices of a plan (25 * 24 for 600 points) never reach the Stockham kernels that a batch runs."""
+    _run(_build(tmp_path, "tune_cache"))
