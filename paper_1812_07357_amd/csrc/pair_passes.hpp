@@ -72,15 +72,17 @@ __device__ __forceinline__ void pair_xfwd_body(const Src& S) {
     // stage A: rows a = ybase + 2c, b = a + 1 of line c as one complex line, straight from the source
     {
       const int c = fdiv(tid, P.fb), j = tid - c * RB;
-      const bool active = c < nc;
       const int ya = ybase + 2 * c;
-      int ra = ya, rb = ya + 1;
+      // lines past the last row are left out (nothing of them is stored); the row past an odd NY is zero: row a
+      // stands in for its loads, as an offset that is out of range by itself would not stay so with a column added
+      const bool active = c < nc && ya < NY, hasb = ya + 1 < NY;
+      int ra = ya, rb = hasb ? ya + 1 : ya;
       if (p.gather) {
-        ra = fmod_i(p.y0 + ya, p.fd_GY);
-        rb = fmod_i(p.y0 + ya + 1, p.fd_GY);
+        ra = fmod_i(p.y0 + ra, p.fd_GY);
+        rb = fmod_i(p.y0 + rb, p.fd_GY);
       }
-      const uint32_t oa = ya < NY ? (uint32_t)((zrow + ra) * rowlen) : kOOB;
-      const uint32_t ob = ya + 1 < NY ? (uint32_t)((zrow + rb) * rowlen) : kOOB;
+      const uint32_t oa = (uint32_t)((zrow + ra) * rowlen);
+      const uint32_t ob = (uint32_t)((zrow + rb) * rowlen);
       const rsrc_t src = make_rsrc(p.src[f], p.src_bytes);
       rsrc_t add = src;
       if constexpr (PML) add = make_rsrc(p.add[f < 6 ? f : 0], f < 6 ? p.src_bytes : 0u);
@@ -96,7 +98,8 @@ __device__ __forceinline__ void pair_xfwd_body(const Src& S) {
         chirp_stage_a<CLASS, -1, false>(lds, P, c, j, active, [&](auto, int t) PSATD_INLINE {
           const bool in = j + RB * t < N;
           const uint32_t xs = in ? (uint32_t)xo[RB * t] : 0u;
-          return cx<T>{load(in ? oa + xs : kOOB), load(in ? ob + xs : kOOB)};
+          const T a = load(in ? oa + xs : kOOB), b = load(in ? ob + xs : kOOB);
+          return cx<T>{a, hasb ? b : T(0)};
         });
         __syncthreads();
         chirp_stage_b<CLASS, -1>(lds, tw, P, cb, kb, cb < nc);
@@ -107,7 +110,8 @@ __device__ __forceinline__ void pair_xfwd_body(const Src& S) {
       } else {
         pair_stage_a<CLASS, -1, false>(lds, P, c, j, active, [&](auto, int t) PSATD_INLINE {
           const uint32_t xs = (uint32_t)xo[RB * t];
-          return cx<T>{load(oa + xs), load(ob + xs)};
+          const T a = load(oa + xs), b = load(ob + xs);
+          return cx<T>{a, hasb ? b : T(0)};
         });
         __syncthreads();
         pair_stage_b<CLASS, -1, true>(lds, tw, P, cb, kb, cb < nc, [&](int t, cx<T> v) PSATD_INLINE {
@@ -388,7 +392,7 @@ __device__ __forceinline__ void pair_xinv_body(const Src& S) {
         const int kx = up ? N - i : i;
         cx<T> x, y;
         gm<T>::ldc2(src, in ? base + __umul24((uint32_t)kx, (uint32_t)NY) : kOOB, x, y);
-        if (!hasb) y = {T(0), T(0)};  // the row past an odd interior
+        if (!(in && hasb)) y = {T(0), T(0)};  // the row past an odd interior; past the line (chirp-z)
         // +1, -1 for the conjugate, 0 where the bin is its own conjugate (imaginary part dropped)
         const T s = (i == 0 || 2 * i == N) ? T(0) : (up ? T(-1) : T(1));
         return cx<T>{x.re - s * y.im, y.re + s * x.im};

@@ -71,3 +71,32 @@ def test_batch_of_direct_and_chirp_boxes_equals_single_boxes(lib):
         assert torch.equal(got[at], one[at]), plan.box
         plan.close()
     batch.close()
+
+
+@pytest.mark.parametrize("precision", ["fp64", "fp32"])
+@pytest.mark.parametrize("nx", [24, 600, 38, 311, 245])
+def test_odd_boxes_read_nothing_outside_them(lib, nx, precision):
+    """The last row of an odd box has no partner: whatever the cells outside the box hold, its fields are
+    the same bit for bit (direct, chirp-z and Stockham x lines; alone and in a batch)."""
+    import torch
+
+    dtype = torch.float64 if precision == "fp64" else torch.float32
+    box = dict(origin=(5, 7, 6), interior=(nx - 4, 9, 7), nguard=2, order=8)   # nx x 13 x 11 cells
+    gdims = (nx + 12, 40, 24)
+    f = torch.as_tensor(synth.random_fields(synth.rng_for(214, nx), gdims[::-1]), dtype=dtype, device="cuda")
+    covered = torch.zeros(gdims[::-1], dtype=torch.bool, device="cuda")
+    covered[4:15, 5:18, 3:3 + nx] = True
+    plan = lib.Plan(*box["interior"], nguard=2, order=8, dt=0.5, precision=precision)
+    batch = lib.Batch([box], gdims, dt=0.5, precision=precision)
+    at = (slice(0, 6), slice(6, 13), slice(7, 16), slice(5, 1 + nx))
+    for name, advance in (("plan", lambda g: plan.step_g1(g, box["origin"])), ("batch", batch.step)):
+        out = []
+        for outside in (0.0, float("nan")):
+            g = torch.where(covered, f, torch.full_like(f, outside))
+            advance(g)
+            torch.cuda.synchronize()
+            out.append(g[at].clone())
+        assert torch.isfinite(out[1]).all(), name
+        assert torch.equal(out[0], out[1]), name
+    plan.close()
+    batch.close()
