@@ -39,6 +39,7 @@
 
 #include "../../include/psatd.h"
 #include "internal.hpp"
+#include "row_run.hpp"
 
 namespace psatd {
 namespace {
@@ -135,21 +136,6 @@ __device__ __forceinline__ void grid_points(Points<K, T>& g, const PicArgs<T>& a
     g.ys[c] = fold(fy + c, a.gy) * a.gx;
     g.zs[c] = fold(fz + c, a.gz) * a.gy * a.gx;
   }
-}
-
-// K + 1 consecutive values of a row, read with one multi-word load (4-byte aligned vectors)
-template <int K, typename T>
-struct RowRun {
-  T v[K + 1];
-};
-template <int K, typename T>
-__device__ __forceinline__ RowRun<K, T> load_run(const T* p) {
-  typedef T vec_t __attribute__((ext_vector_type(K + 1), aligned(alignof(T))));
-  const vec_t x = *reinterpret_cast<const vec_t*>(p);
-  RowRun<K, T> r;
-#pragma unroll
-  for (int c = 0; c <= K; ++c) r.v[c] = x[c];
-  return r;
 }
 
 template <int K, typename T>

@@ -7,6 +7,7 @@ radices or tables is checked over whole ranges of sizes without a GPU.
 """
 
 import os
+import re
 import shutil
 import subprocess
 
@@ -45,3 +46,34 @@ def test_every_pml_z_pass_has_its_tables(tmp_path):
 def test_plans_and_batches_share_a_tune_cache(tmp_path):
     """Pair radices of a plan (25 * 24 for 600 points) never reach the Stockham kernels that a batch runs."""
     _run(_build(tmp_path, "tune_cache"))
+
+
+_ROW_KERNELS = """
+#include "row_run.hpp"
+#define KERNEL(K, T, NAME) \\
+  extern "C" __global__ void NAME(const T* p, T* out) { \\
+    const auto r = psatd::load_run<K>(p + threadIdx.x); \\
+    for (int c = 0; c <= K; ++c) out[(K + 1) * threadIdx.x + c] = r.v[c]; \\
+  }
+KERNEL(1, float, k1_float) KERNEL(2, float, k2_float) KERNEL(3, float, k3_float)
+KERNEL(1, double, k1_double) KERNEL(2, double, k2_double) KERNEL(3, double, k3_double)
+"""
+
+
+def test_a_row_of_the_gather_is_read_and_no_value_more(tmp_path):
+    """The words that the loads of a particle's row cover, from the assembly: K + 1 values, not a whole
+    power of two of them (the fourth value after the last row of an array may not be mapped)."""
+    if not os.path.exists(HIPCC):
+        pytest.skip("needs hipcc")
+    src, out = tmp_path / "rows.hip", tmp_path / "rows.s"
+    src.write_text(_ROW_KERNELS)
+    cmd = [HIPCC, "-std=c++17", "-O3", "--offload-arch=gfx950", "--offload-device-only", "-S", f"-I{PKG}/csrc", str(src),
+           "-o", str(out)]
+    r = subprocess.run(cmd, capture_output=True, text=True)
+    assert r.returncode == 0, r.stderr[-4000:]
+    text = out.read_text()
+    for k in (1, 2, 3):
+        for real, words in (("float", 1), ("double", 2)):
+            body = re.search(rf"^k{k}_{real}:(.*?)s_endpgm", text, re.S | re.M).group(1)
+            loads = re.findall(r"\b(?:global|flat|buffer)_load_dword(?:x(\d))?\b", body)
+            assert loads and sum(int(n or 1) for n in loads) == (k + 1) * words, (k, real, loads)
