@@ -77,3 +77,12 @@ def test_a_row_of_the_gather_is_read_and_no_value_more(tmp_path):
             body = re.search(rf"^k{k}_{real}:(.*?)s_endpgm", text, re.S | re.M).group(1)
             loads = re.findall(r"\b(?:global|flat|buffer)_load_dword(?:x(\d))?\b", body)
             assert loads and sum(int(n or 1) for n in loads) == (k + 1) * words, (k, real, loads)
+
+
+def test_signed_zeros_are_given_up_in_the_chirp_z_units_only():
+    from paper_1812_07357_amd import build_lib
+
+    assert "-fno-signed-zeros" not in build_lib.FLAGS
+    for src, name, extra in build_lib.SOURCES:
+        chirp = src == "passes.hip" and any(f"-DPSATD_UNIT={u}" in extra for u in (8, 9))
+        assert ("-fno-signed-zeros" in extra) == chirp, name
