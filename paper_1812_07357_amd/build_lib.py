@@ -31,23 +31,23 @@ FLAGS = [
     f"-I{os.path.join(ROOT, 'include')}",
 ]
 
-# (source, object name, extra flags).  passes.hip is compiled once per unit and precision, the
-# pair kernels (units 7..9) also once per pass, so that the large pass kernels build in
-# parallel; the slowest units come first.
-_PASS_UNITS = [(u, part, f"{name}_{kind}", prec)
-               for part, name in ((3, "zpush"), (2, "ypass"), (1, "xfwd"), (4, "xinv"))
-               for u, kind in ((7, "pair"), (9, "pair_batch"), (8, "chirp"))
-               for prec in ("float", "double")]
-_PASS_UNITS += [(u, 0, name, prec)
-                for u, name in ((1, "xfwd"), (2, "ypass"), (3, "zpush"), (4, "zpush_batch"), (5, "xinv"), (6, "zpush_pml"))
-                for prec in ("float", "double")]
-# Units with chirp-z lines (8, and 9 of the batches): their zero padding folds out of the butterflies
-# where -0 and +0 are the same value, which they are for a field.  The Stockham y pass spills more with the flag
-# (FP32, chirp-z lines of 579 to 645 points 11 % slower), the direct pairs gain nothing.
+# Chirp-z lines: their zero padding folds out of the butterflies where -0 and +0 are the same value, which
+# they are for a field.  The Stockham y pass spills more with the flag (FP32, chirp-z lines of 579 to 645 points
+# 17 % slower), the direct pairs gain nothing.  (A kernel and its form for batches are compiled alike: their
+# results are the same bit for bit.)
 _CHIRP_FLAGS = ["-fno-signed-zeros"]
-SOURCES = [("passes.hip", f"passes_{name}_{prec}",
-            [f"-DPSATD_UNIT={u}", f"-DPSATD_REAL={prec}"] + ([f"-DPSATD_PART={part}"] if part else []) + (_CHIRP_FLAGS if u >= 8 else []))
-           for u, part, name, prec in _PASS_UNITS]
+# (source, object name, extra flags).  passes.hip is compiled once per unit and precision, the
+# pair kernels (units 7..9) also once per pass, those of batches per class, so that the large pass
+# kernels build in parallel; the slowest units come first.
+_PAIR_UNITS = (("pair", ["-DPSATD_UNIT=7"]), ("pair_batch", ["-DPSATD_UNIT=9", "-DPSATD_CLASS=0"]),
+               ("chirp", ["-DPSATD_UNIT=8", *_CHIRP_FLAGS]),
+               ("chirp_batch", ["-DPSATD_UNIT=9", "-DPSATD_CLASS=2", *_CHIRP_FLAGS]))
+_PASS_UNITS = [(f"{name}_{kind}", [*unit, f"-DPSATD_PART={part}"])
+               for part, name in ((3, "zpush"), (2, "ypass"), (1, "xfwd"), (4, "xinv")) for kind, unit in _PAIR_UNITS]
+_PASS_UNITS += [(name, [f"-DPSATD_UNIT={u}"])
+                for u, name in ((1, "xfwd"), (2, "ypass"), (3, "zpush"), (4, "zpush_batch"), (5, "xinv"), (6, "zpush_pml"))]
+SOURCES = [("passes.hip", f"passes_{name}_{prec}", [*extra, f"-DPSATD_REAL={prec}"])
+           for name, extra in _PASS_UNITS for prec in ("float", "double")]
 SOURCES += [(src, os.path.splitext(src)[0], []) for src in ("tables.hip", "guards.hip", "plan.hip", "mlp.hip", "pic.hip", "pml.hip")]
 
 

@@ -579,7 +579,8 @@ void launch_xinv_batch(const BatchArgs<XInvParams<T>>& a, int nthreads, size_t l
 // Explicit instantiations.  The build compiles this file once per unit and precision
 // (-DPSATD_UNIT=1..9 -DPSATD_REAL=float|double) so that the units compile in parallel:
 // 1..6 the Stockham kernels of one pass, 7 the direct and 8 the chirp-z pair kernels, 9 those
-// of batches; -DPSATD_PART=1..4 takes one pass (x forward, y, z, x inverse) of a unit 7..9.
+// of batches; -DPSATD_PART=1..4 takes one pass (x forward, y, z, x inverse) of a unit 7..9 and
+// -DPSATD_CLASS=0|2 one class of unit 9.
 #define PSATD_INST_1(T)                                                                     \
   template void launch_xfwd<T>(const XFwdParams<T>&, hipStream_t);                          \
   template void launch_xfwd_batch<T>(const BatchArgs<XFwdParams<T>>&, size_t, hipStream_t); \
@@ -605,7 +606,9 @@ void launch_xinv_batch(const BatchArgs<XInvParams<T>>& a, int nthreads, size_t l
 PSATD_CAT(PSATD_INST_, PSATD_UNIT)(PSATD_REAL)
 #else
 // units 7 and 8: direct and chirp-z pairs (both classes), 9: batches (classes 0 and 2)
-#if PSATD_UNIT == 9
+#if PSATD_UNIT == 9 && defined(PSATD_CLASS)
+#define PSATD_PAIR(part) PSATD_CAT(PSATD_PAIR_BATCH_, part)(PSATD_REAL, PSATD_CLASS)
+#elif PSATD_UNIT == 9
 #define PSATD_PAIR(part) \
   PSATD_CAT(PSATD_PAIR_BATCH_, part)(PSATD_REAL, 0) PSATD_CAT(PSATD_PAIR_BATCH_, part)(PSATD_REAL, 2)
 #elif PSATD_UNIT == 8
