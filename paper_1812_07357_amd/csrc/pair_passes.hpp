@@ -396,11 +396,11 @@ __device__ __forceinline__ void pair_xinv_body(const Src& S) {
       const uint32_t base = (uint32_t)(zs * NXH * NY + ya);
       auto load = [&](auto, int t) PSATD_INLINE {
         const int i = j + RB * t;
-        const bool up = 2 * i > N, in = hasa && i < N;
+        const bool up = 2 * i > N, in = hasa && (!chirp_class(CLASS) || i < N);
         const int kx = up ? N - i : i;
         cx<T> x, y;
         gm<T>::ldc2(src, in ? base + __umul24((uint32_t)kx, (uint32_t)NY) : kOOB, x, y);
-        if (!(in && hasb)) y = {T(0), T(0)};  // the row past an odd interior; past the line (chirp-z)
+        if (!(chirp_class(CLASS) ? in && hasb : hasb)) y = {T(0), T(0)};  // the row past an odd interior; past the line
         // +1, -1 for the conjugate, 0 where the bin is its own conjugate (imaginary part dropped)
         const T s = (i == 0 || 2 * i == N) ? T(0) : (up ? T(-1) : T(1));
         return cx<T>{x.re - s * y.im, y.re + s * x.im};
