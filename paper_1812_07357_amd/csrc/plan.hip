@@ -373,6 +373,7 @@ struct psatd_plan {
   // complex x lines, y lines, (kx, ky) columns.
   PairAxis pair[3];
   int pair_nl[3] = {0, 0, 0};
+  int pair_nl5 = 0;  // x lines of a P5 tile (pair_nl[0]: P1)
   bool large_radices = true;
   bool interleaved = true;  // layout B [kx][ky][field][z]; false: [field][kx][ky][z] (see build_plan)
   double* kd = nullptr;  // FP64 modified k: kx (NXH), ky (NY), kz (NZ)
@@ -495,9 +496,13 @@ void choose_z_tile(psatd_plan* p, const LineSchedule& szs, int em, size_t cs) {
 // side, more for short lines (at least a wavefront per block); y: the lines of 128 contiguous
 // bytes, more for short lines (about 4608 points in FP32, 2304 in FP64).  x tiles of as many
 // points ran slower: 288-point lines 205 us at 16 lines per tile, 174 us at 8 (box 288x160x160).
+// Rows of layout A off the 64-byte lines of memory (`ragged`): x forward tiles of twice the lines, as the
+// lines at both ends of a run are written in parts, by two tiles (256x705x40: P1 in FP32 294 -> 207
+// us, 200x705x40 226 -> 166, in FP64 324 -> 272).  The x inverse only reads and keeps the smaller tile (126
+// against 139 us), chirp-z lines too (205x705x40: 276 against 298).
 // z: the columns of about 320 points, fewer where the block or (several columns) 80 KB of LDS
 // is exceeded.  0: the pair does not fit this device.
-int pair_tile(const PairAxis& a, int axis, bool fp64, int fields) {
+int pair_tile(const PairAxis& a, int axis, bool fp64, int fields, bool ragged = false) {
   const size_t cs = fp64 ? 16 : 8;
   const int tmax = pair_threads_max(fp64, a.cls, axis == 2);
   if (axis == 2) {
@@ -507,7 +512,7 @@ int pair_tile(const PairAxis& a, int axis, bool fp64, int fields) {
         return c;
     return 0;
   }
-  const int points = fp64 ? 2304 : 4608, least = 128 / (int)(axis == 0 ? 2 * cs : cs);
+  const int points = fp64 ? 2304 : 4608, least = (ragged ? 256 : 128) / (int)(axis == 0 ? 2 * cs : cs);
   const size_t cap = std::min<size_t>(80 * 1024, lds_limit());
   auto fits = [&](int nl) {
     return nl * a.ra <= tmax &&
@@ -526,10 +531,12 @@ int pair_report_tile(const psatd_plan* p, int axis) {
 
 // Takes pair `a` for an axis if it fits (tile and LDS).
 bool take_pair(psatd_plan* p, int axis, const PairAxis& a) {
-  const int nl = pair_tile(a, axis, p->fp64 != 0, 11);
+  const bool ragged = axis == 0 && !a.blue && (long long)p->NY * 2 * (long long)p->rsize % 64 != 0;
+  const int nl = pair_tile(a, axis, p->fp64 != 0, 11, ragged);
   if (nl < 1) return false;
   p->pair[axis] = a;
   p->pair_nl[axis] = nl;
+  if (axis == 0) p->pair_nl5 = pair_tile(a, axis, p->fp64 != 0, 11);
   if (axis == 2) p->zcols = nl;
   return true;
 }
@@ -1019,10 +1026,10 @@ void build_step(psatd_plan* p, const StepIO& io, StepParams<T>& sp) {
   x5.nthreads = p->x5threads;
   x5.fft = line_fft<T>(p->ax);
   if (p->pair[0].ra) {
-    x5.pair = x1.pair;
-    x5.pnl = x1.pnl;
-    x5.pnl_sh = x1.pnl_sh;
-    x5.pthreads = x1.pthreads;
+    x5.pair = pair_fft<T>(p->pair[0], 0, p->pair_nl5);
+    x5.pnl = p->pair_nl5;
+    x5.pnl_sh = log2_of(x5.pnl);
+    x5.pthreads = pair_block(x5.pnl, x5.pair.ra);
     x5.ty = 2 * x5.pnl;
   }
   x5.ytiles = (io.y_hi - io.y_lo + x5.ty - 1) / x5.ty;
