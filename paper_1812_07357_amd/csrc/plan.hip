@@ -294,6 +294,36 @@ std::vector<PairAxis> ranked_pairs(int n, bool large) {
   return out;
 }
 
+// Whether the Stockham kernel of a line beats its pair (`stockham_m`: the length that it transforms).
+// Few lengths: below, the time of the axis's own passes on the pair over that on the Stockham
+// kernels, boxes of the length by 96x96 or 64x64 cells.
+bool stockham_faster(const PairAxis& a, int axis, bool fp64, int stockham_m) {
+  const bool large = a.cls == 1;
+  if (axis == 2) {
+    // Large radices leave two FP32 wavefronts per SIMD, and eleven short lines are too few
+    // threads to fill them: 125 = 25 * 5 1.77, 250 1.48, 363 1.27, 416 1.19, 429 1.28; 442 0.95, 448 1.00, 459
+    // 0.80, 510 1.06, 612 0.76.
+    if (!fp64 && large && a.m < 440) return true;
+    // FP64: only where stage A has five or seven threads per line (125 1.04, 175 1.07, 243 0.94)
+    if (large && a.rb < 8) return true;
+    // The longest chirp-z pair of the small radices where Stockham stages pad to a tenth less (241..256
+    // cells: 576 = 24 * 24 against 512) 1.25; with the same padding 0.65 (257 cells on), shorter ones 1.07 at most.
+    return !fp64 && a.cls == 2 && a.m > 512 && 10 * stockham_m < 9 * a.m;
+  }
+  // one 17-point butterfly per line or two: x 1.10 (FP64 1.42), y 1.39 (1.62); 34 = 17 * 2 0.91 (1.11), 1.07
+  // (1.22); 51 0.97 (1.08), 1.04 (0.92)
+  if (a.ra == 17 && a.rb <= 2) return fp64 || axis == 1 || a.rb == 1;
+  if (!large) return false;
+  // 125 and 175: x 1.12 and 1.17 (FP64 1.24, 0.91), y 1.21 and 0.99 (0.68, 0.74)
+  if (a.rb < 8) return !fp64 || (axis == 0 && a.rb < 6);
+  // 33, 34 and 36 points with a short stage B.  x: 363 = 33 * 11 1.59 (1.19), 429 1.37 (1.21), 495 1.25
+  // (1.02), 561 1.35 (1.03), 612 = 36 * 17 1.32 (1.00), 714 1.38 (1.01); y: 1.41 (0.86), 1.32 (0.68), 1.01
+  // (0.67), 1.21 (0.79), 0.92 (0.73), 1.34 (0.79).  From 33 * 32 on they win again (0.81 and 0.93), except in
+  // FP64 along y with 33 points on either side: 1056 1.11, 1089 1.11, 1122 1.28, 1188 1.15.
+  if (!fp64) return a.ra >= 33 && a.rb < 25 && (axis == 0 || a.ra != 36);
+  return axis == 0 ? a.ra >= 33 && a.rb < 15 : a.rb >= 32 && (a.ra == 33 || a.rb == 33);
+}
+
 // LDS slots per line of a pair on an axis with `nl` lines per tile (see pair_line).
 int pair_slots(const PairAxis& a, int axis, int nl, bool fp64) {
   const int pitch = fp64 ? pair_pitch<double>(a.rb) : pair_pitch<float>(a.rb);
@@ -477,12 +507,12 @@ int z_group(const LineSchedule& s, int zt, int em, size_t cs, int nlines) {
   return std::max(1, fit_lines(s, zt, em, cs, nlines, SIZE_MAX));
 }
 
-// Columns and threads of a z tile: about 320 points of line per tile, the
+// Columns (`most` at most) and threads of a z tile: about 320 points of line per tile, the
 // smallest block that fits.
-void choose_z_tile(psatd_plan* p, const LineSchedule& szs, int em, size_t cs) {
+void choose_z_tile(psatd_plan* p, const LineSchedule& szs, int em, size_t cs, int most) {
   p->zthreads = 0;
   p->zcols = 0;
-  for (int c = std::max(1, std::min(16, 320 / p->NZ)); c >= 1 && !p->zthreads; --c)
+  for (int c = std::max(1, std::min(most, 320 / p->NZ)); c >= 1 && !p->zthreads; --c)
     for (int zt : kZThreads)
       if (z_fits(szs, zt, em, cs, c)) {
         p->zthreads = zt;
@@ -644,7 +674,7 @@ int build_plan(const psatd_plan_desc* d, psatd_plan** out, bool large = true) {
   p->ty1 = 2 * std::max(nc1, 0);
   p->ty5 = x_inv_tile(p, sxs, em, cs, p->ty1, lds_small);
   p->nl_y = fit_lines(sys, nth, em, cs, y_line_cap(p->NY), lds_small);
-  choose_z_tile(p, szs, em, cs);
+  choose_z_tile(p, szs, em, cs, large ? 1 : 16);  // (the z kernel of a single box holds one column)
   if (p->ty1 <= 0 || p->ty5 <= 0 || p->nl_y <= 0 || p->zthreads == 0) {
     free_plan(p);
     return fail(PSATD_EUNSUPPORTED, "box %dx%dx%d does not fit the LDS / register tiling of this build", p->NX,
@@ -653,12 +683,16 @@ int build_plan(const psatd_plan_desc* d, psatd_plan** out, bool large = true) {
   // One kx plane of layout B is addressed through 32-bit offsets; a plane of 4 GiB or more
   // (a thin box) keeps its fields apart, and its z pass stays on the Stockham kernel.
   p->interleaved = (double)p->NY * 12.0 * p->NZ * (double)cs < 4294967296.0;
+  Axis* const axes[3] = {&p->ax, &p->ay, &p->az};
   {
     const int n[3] = {p->NX, p->NY, p->NZ};
     for (int a = 0; a < 3; ++a) {
       if (a == 2 && !p->interleaved) continue;
-      for (const PairAxis& c : ranked_pairs(n[a], large))
-        if (take_pair(p, a, c)) break;
+      for (const PairAxis& c : ranked_pairs(n[a], large)) {
+        if (pair_tile(c, a, p->fp64 != 0, 11) < 1) continue;
+        if (!stockham_faster(c, a, p->fp64 != 0, axes[a]->sch.n)) (void)take_pair(p, a, c);
+        break;
+      }
     }
   }
   // Every array is addressed through 32-bit byte offsets.
@@ -669,7 +703,6 @@ int build_plan(const psatd_plan_desc* d, psatd_plan** out, bool large = true) {
   }
   const size_t npts = (size_t)p->npts;
   const size_t tws = p->fp64 ? sizeof(Tw<double>) : sizeof(Tw<float>);
-  Axis* const axes[3] = {&p->ax, &p->ay, &p->az};
   for (int k = 0; k < 3; ++k) {
     Axis* const a = axes[k];
     PairAxis& q = p->pair[k];

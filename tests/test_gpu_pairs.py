@@ -100,3 +100,29 @@ def test_odd_boxes_read_nothing_outside_them(lib, nx, precision):
         assert torch.equal(out[0], out[1]), name
     plan.close()
     batch.close()
+
+
+# lengths with a pair that the Stockham kernels beat on at least one axis, and their neighbours that keep it
+EITHER = [17, 34, 51, 125, 175, 241, 243, 250, 256, 257, 363, 390, 429, 495, 510, 512, 561, 612, 714]
+
+
+@pytest.mark.parametrize("precision", ["fp64", "fp32"])
+@pytest.mark.parametrize("axis", [0, 1, 2])
+def test_lengths_that_keep_the_stockham_kernels_match_oracle(lib, axis, precision):
+    import torch
+
+    kinds = set()
+    for n in EITHER:
+        edges = [7, 5]
+        edges.insert(axis, n)
+        plan = lib.Plan(*edges, nguard=0, order=8, dx=1.0, dt=0.5, precision=precision)
+        kinds.add(bool(plan.query(lib.Q_TWO_STAGE) >> (0, 1, 2)[axis] & 1))
+        f = synth.random_fields(synth.rng_for(215 + axis, n), plan.box_shape)
+        ref = step.box_step(f, 1.0, 0.5, 8)
+        g = torch.as_tensor(f, dtype=plan.dtype, device="cuda")
+        plan.push_fields(g)
+        torch.cuda.synchronize()
+        err = np.abs(g[0:6].double().cpu().numpy() - ref).max() / np.abs(ref).max()
+        assert err <= (1e-12 if precision == "fp64" else 2e-5), (edges, err)
+        plan.close()
+    assert kinds == {True, False}
