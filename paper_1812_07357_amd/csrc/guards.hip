@@ -21,17 +21,25 @@ struct PtrSet {
   void* out[kMaxFields];
 };
 
-// Fill and interior copy move rows: one wavefront per row (y, z) and kFields arrays, so that the
+// Fill and interior copy move rows: a row (y, z) of kFields arrays per 1 << sh lanes, so that the
 // divisions are made once per row and column and a lane has kFields loads in flight.  With one thread per
 // value, each dividing its index four times, the fill of 288x160x160 from 256x128x128 in FP32
-// (eleven arrays) took 0.285 ms (now 0.130) and the copy back of six 0.102 (now 0.042).
-constexpr int kRows = kT / 64, kFields = 4;
+// (eleven arrays) took 0.285 ms (now 0.140) and the copy back of six 0.087 (now 0.038).  A row takes the
+// lanes of the next power of two and at most a wavefront: with a wavefront for every row, boxes of few cells along x
+// left most lanes idle (1x512x512, eleven arrays: 178 us, now 15; 8x256x256: 53 us, now 20).
+constexpr int kFields = 4;
+
+int row_lanes(int n) {  // log2
+  int sh = 0;
+  while (sh < 6 && (1 << sh) < n) ++sh;
+  return sh;
+}
 
 template <typename T>
 __device__ __forceinline__ void move_row(const PtrSet& ps, int nfields, long long src, long long dst, int n, int sx,
-                                         int GX, bool wrap_src) {
-  const int f0 = blockIdx.y * kFields;
-  for (int i = threadIdx.x & 63; i < n; i += 64) {
+                                         int GX, bool wrap_src, int sh) {
+  const int f0 = blockIdx.y * kFields, lanes = 1 << sh;
+  for (int i = threadIdx.x & (lanes - 1); i < n; i += lanes) {
     const int xg = (int)(((unsigned)sx + (unsigned)i) % (unsigned)GX);
     const long long is = src + (wrap_src ? xg : i), id = dst + (wrap_src ? i : xg);
     T v[kFields];
@@ -46,23 +54,23 @@ __device__ __forceinline__ void move_row(const PtrSet& ps, int nfields, long lon
 
 template <typename T>
 __global__ void __launch_bounds__(kT) k_fill(PtrSet ps, int nfields, int BX, int BY, int BZ, int sx, int sy, int sz,
-                                             int GX, int GY, int GZ) {
-  const long long r = (long long)blockIdx.x * kRows + (threadIdx.x >> 6);
+                                             int GX, int GY, int GZ, int sh) {
+  const long long r = (long long)blockIdx.x * (kT >> sh) + (threadIdx.x >> sh);
   if (r >= (long long)BY * BZ) return;
   const int k = (int)(r / BY), j = (int)(r - (long long)k * BY);
   const long long yg = ((long long)sy + j) % GY, zg = ((long long)sz + k) % GZ;
-  move_row<T>(ps, nfields, (zg * GY + yg) * GX, r * BX, BX, sx, GX, true);
+  move_row<T>(ps, nfields, (zg * GY + yg) * GX, r * BX, BX, sx, GX, true, sh);
 }
 
 template <typename T>
 __global__ void __launch_bounds__(kT) k_merge_copy(PtrSet ps, int nfields, int BX, int BY, int gx, int gy, int gz,
                                                    int nx, int ny, int nz, int ox, int oy, int oz, int GX, int GY,
-                                                   int GZ) {
-  const long long r = (long long)blockIdx.x * kRows + (threadIdx.x >> 6);
+                                                   int GZ, int sh) {
+  const long long r = (long long)blockIdx.x * (kT >> sh) + (threadIdx.x >> sh);
   if (r >= (long long)ny * nz) return;
   const int k = (int)(r / ny), j = (int)(r - (long long)k * ny);
   const long long yg = ((long long)oy + j) % GY, zg = ((long long)oz + k) % GZ;
-  move_row<T>(ps, nfields, ((long long)(k + gz) * BY + (j + gy)) * BX + gx, (zg * GY + yg) * GX, nx, ox, GX, false);
+  move_row<T>(ps, nfields, ((long long)(k + gz) * BY + (j + gy)) * BX + gx, (zg * GY + yg) * GX, nx, ox, GX, false, sh);
 }
 
 // One thread per global cell covered by the box; pre-images along an axis are a, a+G, a+2G, ... < B.
@@ -102,13 +110,14 @@ void launch_guard_fill(const void* const* g1, void* const* box, int nfields, int
     ps.in[f] = g1[f];
     ps.out[f] = box[f];
   }
-  dim3 grid((unsigned)(((long long)bd[1] * bd[2] + kRows - 1) / kRows), (unsigned)((nfields + kFields - 1) / kFields));
+  const int sh = row_lanes(bd[0]), rows = kT >> sh;
+  dim3 grid((unsigned)(((long long)bd[1] * bd[2] + rows - 1) / rows), (unsigned)((nfields + kFields - 1) / kFields));
   if (esize == 8)
     hipLaunchKernelGGL(k_fill<double>, grid, dim3(kT), 0, s, ps, nfields, bd[0], bd[1], bd[2], start[0], start[1], start[2],
-                       gd[0], gd[1], gd[2]);
+                       gd[0], gd[1], gd[2], sh);
   else
     hipLaunchKernelGGL(k_fill<float>, grid, dim3(kT), 0, s, ps, nfields, bd[0], bd[1], bd[2], start[0], start[1], start[2],
-                       gd[0], gd[1], gd[2]);
+                       gd[0], gd[1], gd[2], sh);
 }
 
 void launch_guard_merge(const void* const* box, void* const* g1, int nfields, int esize, const int bd[3],
@@ -120,14 +129,15 @@ void launch_guard_merge(const void* const* box, void* const* g1, int nfields, in
     ps.out[f] = g1[f];
   }
   if (mode == 0) {
-    dim3 grid((unsigned)(((long long)interior[1] * interior[2] + kRows - 1) / kRows),
+    const int sh = row_lanes(interior[0]), rows = kT >> sh;
+    dim3 grid((unsigned)(((long long)interior[1] * interior[2] + rows - 1) / rows),
               (unsigned)((nfields + kFields - 1) / kFields));
     if (esize == 8)
       hipLaunchKernelGGL(k_merge_copy<double>, grid, dim3(kT), 0, s, ps, nfields, bd[0], bd[1], guard[0], guard[1], guard[2],
-                         interior[0], interior[1], interior[2], origin[0], origin[1], origin[2], gd[0], gd[1], gd[2]);
+                         interior[0], interior[1], interior[2], origin[0], origin[1], origin[2], gd[0], gd[1], gd[2], sh);
     else
       hipLaunchKernelGGL(k_merge_copy<float>, grid, dim3(kT), 0, s, ps, nfields, bd[0], bd[1], guard[0], guard[1], guard[2],
-                         interior[0], interior[1], interior[2], origin[0], origin[1], origin[2], gd[0], gd[1], gd[2]);
+                         interior[0], interior[1], interior[2], origin[0], origin[1], origin[2], gd[0], gd[1], gd[2], sh);
   } else {
     int start[3];
     for (int a = 0; a < 3; ++a) start[a] = (int)((((long long)origin[a] - guard[a]) % gd[a] + gd[a]) % gd[a]);

@@ -242,3 +242,11 @@ def test_config1_ten_steps_fp64(lib):
     assert diagnostics.rel_l2(got[0:3], ref[0:3]) <= 1e-12
     assert diagnostics.rel_l2(got[3:6], ref[3:6]) <= 1e-12
     plan.close()
+
+
+@pytest.mark.parametrize("precision", ["fp64", "fp32"])
+@pytest.mark.parametrize("nx", [1, 2, 3, 4, 5, 7, 8, 9, 15, 16, 17, 30, 31, 32, 33])
+def test_guard_rows_that_share_a_wavefront(lib, precision, nx):
+    """Rows of one to 35 cells: several of them per wavefront, with and without guards."""
+    test_guard_rows_of_any_width_and_number_of_arrays(lib, precision, 6, (nx, 7, 5), 1, (6, 9, nx + 3))
+    test_guard_rows_of_any_width_and_number_of_arrays(lib, precision, 11, (nx, 9, 3), 0, (3, 9, nx))
