@@ -367,7 +367,8 @@ int psatd_tune_cache_load(const char* path, int* accepted, int* rejected);
 
 /* Sets (or changes) the layers: width[3] cells per axis (0 = no layer; at
  * most half the box edge), sigma_max >= 0, power >= 0.  The first call
- * allocates the damping tables and twelve box arrays of scratch.
+ * allocates the damping tables, a spectral workspace of twelve fields and,
+ * where the x lines have no radix pair, twelve box arrays of scratch.
  * Synchronises the device. */
 int psatd_pml_set(psatd_plan* plan, const int width[3], double sigma_max, double power);
 

@@ -421,8 +421,8 @@ struct psatd_plan {
   hipEvent_t done = nullptr;
   hipStream_t last_stream = nullptr;
   bool in_flight_known = false;
-  // Two-step PML (psatd_pml_set): damping factors per axis (NX, NY, NZ values), and
-  // six box arrays each for the full fields and for one set of split increments.
+  // Two-step PML (psatd_pml_set): damping factors per axis (NX, NY, NZ values), and where the x
+  // passes are Stockham kernels six box arrays each for the full fields and for one set of split increments.
   bool pml_ready = false;
   void* pml_wsB = nullptr;  // layout B with 12 fields (P3 writes both split sets)
   void* pml_damp[3] = {nullptr, nullptr, nullptr};
@@ -2023,14 +2023,14 @@ int psatd_pml_set(psatd_plan* p, const int width[3], double sigma_max, double po
     if (int rc = check_hip("psatd_pml_set")) return rc;
     if (hipDeviceSynchronize() != hipSuccess) return check_hip("psatd_pml_set");
   }
-  if (!p->pml_ready) {
-    if (int rc = dalloc(p, &p->pml_wsB, (size_t)12 * p->npts * 2 * rs)) return rc;
-    for (int a = 0; a < 3; ++a)
-      if (int rc = dalloc(p, &p->pml_damp[a], (size_t)n[a] * rs)) return rc;
-    for (int f = 0; f < 6; ++f) {
-      if (int rc = dalloc(p, &p->pml_full[f], (size_t)p->ncell * rs)) return rc;
-      if (int rc = dalloc(p, &p->pml_inc[f], (size_t)p->ncell * rs)) return rc;
-    }
+  // (each once: an earlier call may have run out of memory half way)
+  auto once = [&](void** q, size_t bytes) { return *q ? PSATD_OK : dalloc(p, q, bytes); };
+  if (int rc = once(&p->pml_wsB, (size_t)12 * p->npts * 2 * rs)) return rc;
+  for (int a = 0; a < 3; ++a)
+    if (int rc = once(&p->pml_damp[a], (size_t)n[a] * rs)) return rc;
+  for (int f = 0; f < 6 && !p->pair[0].ra; ++f) {
+    if (int rc = once(&p->pml_full[f], (size_t)p->ncell * rs)) return rc;
+    if (int rc = once(&p->pml_inc[f], (size_t)p->ncell * rs)) return rc;
   }
   for (int a = 0; a < 3; ++a) {
     // sigma rises as sigma_max (depth / width)^power over `width` cells at each end

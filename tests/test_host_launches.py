@@ -87,3 +87,7 @@ def test_signed_zeros_are_given_up_in_the_chirp_z_units_only():
     for src, name, extra in build_lib.SOURCES:
         chirp = src == "passes.hip" and ("-DPSATD_UNIT=8" in extra or "-DPSATD_CLASS=2" in extra)
         assert ("-fno-signed-zeros" in extra) == chirp, name
+
+
+def test_layers_hold_no_arrays_that_no_pass_uses(tmp_path):
+    _run(_build(tmp_path, "pml_memory"))
