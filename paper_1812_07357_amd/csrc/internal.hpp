@@ -17,7 +17,8 @@ using i64 = long long;
 //   layout A  [field][z][kx][y]   (y fastest)  -- after the x pass
 //   layout B  [kx][ky][field][z]  (z fastest)  -- after the y pass, k-space push in place
 // In layout B the lines that one k-space column needs (11 fields, 12 with the split
-// fields of the PML) are one contiguous block.  Layout A may hold a slab of z planes only.
+// fields of the PML) are one contiguous block.  After the inverse y pass layout A holds the z planes
+// of the interior only.
 // Every pass reads whole contiguous lines on one side and writes tiles of
 // consecutive lines (a short contiguous run per position) on the other.
 
@@ -32,10 +33,9 @@ template <typename T>
 struct XFwdParams {
   const T* src[11];
   uint32_t src_bytes;    // bytes of each source array
-  cx<T>* dst;            // layout A of the slab; field f starts at dst + f * fsA
-  i64 fsA;               // nzs * NXH * NY
-  uint32_t dst_bytes;    // bytes of one field of the slab
-  int zfirst, nzs;       // z planes of this launch: [zfirst, zfirst + nzs)
+  cx<T>* dst;            // layout A; field f starts at dst + f * fsA
+  i64 fsA;               // NZ * NXH * NY
+  uint32_t dst_bytes;    // bytes of one field
   int NX, NY, NZ, NXH;
   int ty;                // real y-lines per tile (even)
   int ytiles, ntiles;    // tiles per (field, z) and in total
@@ -44,7 +44,7 @@ struct XFwdParams {
                          // G1 offset of every real row) placed after the tile's lines
   int GX, GY, GZ;
   int x0, y0, z0;        // (origin - nguard) mod G, non-negative
-  FastDiv fd_ytiles, fd_nzs, fd_NX, fd_GX, fd_GY, fd_GZ, fd_nc;
+  FastDiv fd_ytiles, fd_NZ, fd_NX, fd_GX, fd_GY, fd_GZ, fd_nc;
   int ld_drow, ld_dcol;  // block stride over (complex line, x) = divmod(threads, NX)
   int wr_drow, wr_dcol;  // block stride over (kx, complex line) = divmod(threads, ty / 2)
   int pnl, pnl_sh, pthreads;  // pair kernels: complex lines per tile (a power of two), its shift, block size
@@ -82,7 +82,7 @@ template <typename T>
 struct ZPushParams {
   cx<T>* b;              // layout B, 11 fields (PML: 12)
   i64 npts;              // NXH * NY * NZ
-  i64 fsB, csB;          // elements between the fields of a column, and between columns
+  i64 csB;               // elements between columns (their fields are NZ apart)
   const T* coef;         // C, S1, X1, X2, X3 each npts, pre-scaled by 1/(NX NY NZ)
   uint32_t coef_bytes;   // bytes of one table
   const T* kx;           // NXH
@@ -116,10 +116,10 @@ struct ZPushParams {
 // arrays or scattered into the interior of G1.
 template <typename T>
 struct XInvParams {
-  const cx<T>* src;      // layout A of the slab
-  i64 npts;              // elements of one field of the slab
-  uint32_t src_bytes;    // bytes of one field of the slab
-  int zfirst, nzs;       // z planes of this launch: [zfirst, zfirst + nzs)
+  const cx<T>* src;      // layout A of the planes [zfirst, zfirst + nzs)
+  i64 npts;              // elements of one field of them
+  uint32_t src_bytes;    // bytes of one field of them
+  int zfirst, nzs;       // z planes of the interior
   T* dst[6];
   uint32_t dst_bytes;    // bytes of each destination array
   int NX, NY, NZ, NXH;

@@ -65,9 +65,8 @@ __device__ __forceinline__ void pair_xfwd_body(const Src& S) {
     const int rowlen = p.gather ? p.GX : N;
     const int q = fdiv(lt, p.fd_ytiles);
     const int ybase = (lt - q * p.ytiles) * (2 * nc);
-    const int f = fdiv(q, p.fd_nzs);
-    const int zs = q - f * p.nzs;  // plane within the slab
-    const int z = p.zfirst + zs;
+    const int f = fdiv(q, p.fd_NZ);
+    const int z = q - f * p.NZ;
     const int zrow = p.gather ? fmod_i(p.z0 + z, p.fd_GZ) * p.GY : z * NY;
     // stage A: rows a = ybase + 2c, b = a + 1 of line c as one complex line, straight from the source
     {
@@ -140,7 +139,7 @@ __device__ __forceinline__ void pair_xfwd_body(const Src& S) {
       const cx<T> va = cscale(sum, T(0.5));
       const cx<T> vb = {T(0.5) * dif.im, T(-0.5) * dif.re};
       const int t = 2 * c;
-      const uint32_t o = (uint32_t)((zs * NXH + kx) * NY + ybase + t);
+      const uint32_t o = (uint32_t)((z * NXH + kx) * NY + ybase + t);
       if (t + 1 < ny_t)
         gm<T>::template stc2<kXStore<T>>(dst, o, va, vb);
       else if (t < ny_t)
@@ -384,7 +383,7 @@ __device__ __forceinline__ void pair_xinv_body(const Src& S) {
     const int q = fdiv(lt, p.fd_ytiles);
     const int ybase = p.y_lo + (lt - q * p.ytiles) * (2 * nc);
     const int f = fdiv(q, p.fd_nz);
-    const int zs = q - f * p.nzs;  // plane within the slab
+    const int zs = q - f * p.nzs;  // plane of the interior
     const int z = p.zfirst + zs;
     {
       // lanes across the lines: the rows of a bin are contiguous

@@ -52,8 +52,8 @@ __device__ __forceinline__ void xfwd_body(const Src& S) {
     const XFwdParams<T>& p = S.box(tile, lt);
     const int q = fdiv(lt, p.fd_ytiles);
     const int ybase = (lt - q * p.ytiles) * p.ty;
-    const int f = fdiv(q, p.fd_nzs);
-    const int zs = q - f * p.nzs, z = p.zfirst + zs;  // plane within the slab, and of the box
+    const int f = fdiv(q, p.fd_NZ);
+    const int z = q - f * p.NZ;
     const int NX = p.NX, NY = p.NY, NXH = p.NXH, ty = p.ty, nc = ty >> 1;
     const int ld = fft_slots(p.fft.sch.n);
     const int nld = nc * NX;
@@ -126,7 +126,7 @@ __device__ __forceinline__ void xfwd_body(const Src& S) {
       const cx<T> va = cscale(sum, T(0.5));
       const cx<T> vb = {T(0.5) * dif.im, T(-0.5) * dif.re};
       const int t = 2 * c;
-      const uint32_t o = (uint32_t)((zs * NXH + kx) * NY + ybase + t);
+      const uint32_t o = (uint32_t)((z * NXH + kx) * NY + ybase + t);
       // streamed: layout A is read back by the y pass after all of it has been written
       if (t + 1 < ny_t)
         gm<T>::template stc2<kXStore<T>>(dst, o, va, vb);
@@ -296,7 +296,7 @@ __device__ __forceinline__ void zpush_body(const Src& S) {
         const int f = MULTI ? fdiv(l, p.fd_ncol) : l, c = MULTI ? l - f * ncol : 0;
         const int z = lane + 64 * i;
         const bool ok = q < items && z < NZ && (!MULTI || c < nct);
-        const rsrc_t rb = make_rsrc(p.b + (i64)(col0 + (ok ? c : 0)) * p.csB + (i64)(ok ? f : 0) * p.fsB,
+        const rsrc_t rb = make_rsrc(p.b + (i64)(col0 + (ok ? c : 0)) * p.csB + (ok ? f : 0) * NZ,
                                     (uint32_t)NZ * (uint32_t)sizeof(cx<T>));
         r[u] = gm<T>::ldc(rb, ok ? (uint32_t)z : kOOB);
       }
@@ -339,7 +339,7 @@ __device__ __forceinline__ void zpush_body(const Src& S) {
     for (int l = wave; l < kOut * ncol; l += nwaves) {
       const int f = MULTI ? fdiv(l, p.fd_ncol) : l, c = MULTI ? l - f * ncol : 0;
       if (MULTI && c >= nct) continue;
-      const rsrc_t rb = make_rsrc(p.b + (i64)(col0 + c) * p.csB + (i64)f * p.fsB, (uint32_t)NZ * (uint32_t)sizeof(cx<T>));
+      const rsrc_t rb = make_rsrc(p.b + (i64)(col0 + c) * p.csB + f * NZ, (uint32_t)NZ * (uint32_t)sizeof(cx<T>));
       for (int z = p.z_lo + lane; z < p.z_hi; z += 64) gm<T>::stc(rb, (uint32_t)z, lds[l * ld + lpad(z)]);
     }
     __syncthreads();
@@ -361,7 +361,7 @@ __device__ __forceinline__ void xinv_body(const Src& S) {
     const int q = fdiv(lt, p.fd_ytiles);
     const int ybase = p.y_lo + (lt - q * p.ytiles) * p.ty;
     const int f = fdiv(q, p.fd_nz);
-    const int zs = q - f * p.nzs, z = p.zfirst + zs;  // plane within the slab, and of the box
+    const int zs = q - f * p.nzs, z = p.zfirst + zs;  // plane of the interior, and of the box
     const int NX = p.NX, NY = p.NY, NXH = p.NXH, nc = p.ty >> 1;
     const int ld = fft_slots(p.fft.sch.n);
     {

@@ -64,10 +64,6 @@ constexpr int kMaxShape = 3;
 constexpr double kMaxCourant = 0.999;
 constexpr int kTileMax = 12;
 
-// half-cell offsets of Ex Ey Ez Bx By Bz Jx Jy Jz rho_old rho_new on the staggered grid
-__constant__ int kOffStag[11][3] = {{1, 0, 0}, {0, 1, 0}, {0, 0, 1}, {0, 1, 1}, {1, 0, 1}, {1, 1, 0},
-                                    {1, 0, 0}, {0, 1, 0}, {0, 0, 1}, {0, 0, 0}, {0, 0, 0}};
-
 template <typename T>
 struct PicArgs {
   int gx, gy, gz;

@@ -405,7 +405,6 @@ struct psatd_plan {
   int pair_nl[3] = {0, 0, 0};
   int pair_nl5 = 0;  // x lines of a P5 tile (pair_nl[0]: P1)
   bool large_radices = true;
-  bool interleaved = true;  // layout B [kx][ky][field][z]; false: [field][kx][ky][z] (see build_plan)
   double* kd = nullptr;  // FP64 modified k: kx (NXH), ky (NY), kz (NZ)
   void* kw = nullptr;    // same at working precision
   void* kwc = nullptr;   // staggered grids: kappa = k_s exp(i k d / 2) per axis index, complex
@@ -634,10 +633,6 @@ void fill_line_tables(const psatd_plan* p, const Axis* a) {
   if (a->blue) launch_bluestein(a->chirp, a->n, a->filt, a->n, a->sch.n, p->fp64, nullptr);
 }
 
-// Layout B strides of plan p for `fields` fields: between the fields of a column, between columns.
-i64 b_field_stride(const psatd_plan* p) { return p->interleaved ? (i64)p->NZ : (i64)p->npts; }
-i64 b_column_stride(const psatd_plan* p, int fields) { return p->interleaved ? (i64)fields * p->NZ : (i64)p->NZ; }
-
 // large: pair classes of large radices (batches run the small ones only).
 int build_plan(const psatd_plan_desc* d, psatd_plan** out, bool large = true) {
   int rc = validate(d);
@@ -680,14 +675,10 @@ int build_plan(const psatd_plan_desc* d, psatd_plan** out, bool large = true) {
     return fail(PSATD_EUNSUPPORTED, "box %dx%dx%d does not fit the LDS / register tiling of this build", p->NX,
                 p->NY, p->NZ);
   }
-  // One kx plane of layout B is addressed through 32-bit offsets; a plane of 4 GiB or more
-  // (a thin box) keeps its fields apart, and its z pass stays on the Stockham kernel.
-  p->interleaved = (double)p->NY * 12.0 * p->NZ * (double)cs < 4294967296.0;
   Axis* const axes[3] = {&p->ax, &p->ay, &p->az};
   {
     const int n[3] = {p->NX, p->NY, p->NZ};
     for (int a = 0; a < 3; ++a) {
-      if (a == 2 && !p->interleaved) continue;
       for (const PairAxis& c : ranked_pairs(n[a], large)) {
         if (pair_tile(c, a, p->fp64 != 0, 11) < 1) continue;
         if (!stockham_faster(c, a, p->fp64 != 0, axes[a]->sch.n)) (void)take_pair(p, a, c);
@@ -826,47 +817,6 @@ struct StepParams {
   XInvParams<T> x5;
 };
 
-// Slabs: P1 and P2 (and P4 and P5) may run on a range of z planes at a time, layout A then
-// holding that range only.
-template <typename T>
-void set_slab(XFwdParams<T>& x, int z0, int nz) {
-  x.zfirst = z0;
-  x.nzs = nz;
-  x.fd_nzs = make_fastdiv(nz);
-  x.fsA = (i64)nz * x.NXH * x.NY;
-  x.dst_bytes = (uint32_t)(x.fsA * (i64)sizeof(cx<T>));
-  x.ntiles = 11 * nz * x.ytiles;
-}
-template <typename T>
-void set_slab(XInvParams<T>& x, int z0, int nz) {
-  x.zfirst = z0;
-  x.nzs = nz;
-  x.fd_nz = make_fastdiv(nz);
-  x.npts = (i64)nz * x.NXH * x.NY;
-  x.src_bytes = (uint32_t)(x.npts * (i64)sizeof(cx<T>));
-  x.ntiles = 6 * nz * x.ytiles;
-}
-template <typename T>
-void set_slab_fwd(YPassParams<T>& y, const psatd_plan* p, int z0, int nz) {
-  y.fs_in = (i64)nz * p->NXH * p->NY;
-  y.in_bytes = (uint32_t)(y.fs_in * (i64)sizeof(cx<T>));
-  y.out += z0;
-  y.out_bytes -= (uint32_t)(z0 * (int)sizeof(cx<T>));
-  y.u_lo = 0;
-  y.u_hi = nz;
-  set_ypass(y, 11);
-}
-template <typename T>
-void set_slab_inv(YPassParams<T>& y, const psatd_plan* p, int z0, int nz) {
-  y.fs_out = (i64)nz * p->NXH * p->NY;
-  y.out_bytes = (uint32_t)(y.fs_out * (i64)sizeof(cx<T>));
-  y.in += z0;
-  y.in_bytes -= (uint32_t)(z0 * (int)sizeof(cx<T>));
-  y.u_lo = 0;
-  y.u_hi = nz;
-  set_ypass(y, 6);
-}
-
 int log2_of(int v) {
   int s = 0;
   while ((1 << s) < v) ++s;
@@ -880,7 +830,8 @@ void build_step(psatd_plan* p, const StepIO& io, StepParams<T>& sp) {
   const long long npts = p->npts;
   const int nth = kLineThreads;
   const int fields = io.pml ? 12 : 11;
-  const i64 fsB = b_field_stride(p), csB = b_column_stride(p, fields);
+  const i64 csB = (i64)fields * NZ;  // layout B: between the columns of a kx plane (their fields are NZ apart)
+  const int nzi = io.z_hi - io.z_lo;  // planes that the inverse passes work on
   cx<T>* A = (cx<T>*)io.wsA;
   cx<T>* B = (cx<T>*)io.wsB;
   const T* kw = (const T*)p->kw;
@@ -924,19 +875,25 @@ void build_step(psatd_plan* p, const StepIO& io, StepParams<T>& sp) {
   }
   x1.ytiles = (NY + x1.ty - 1) / x1.ty;
   x1.fd_ytiles = make_fastdiv(x1.ytiles);
-  set_slab(x1, 0, NZ);
+  x1.fd_NZ = make_fastdiv(NZ);
+  x1.fsA = npts;
+  x1.dst_bytes = (uint32_t)(npts * (i64)sizeof(cx<T>));
+  x1.ntiles = 11 * NZ * x1.ytiles;
 
   YPassParams<T>& y2 = sp.y2;
   y2 = YPassParams<T>{};
   y2.in = A;
   y2.out = B;
-  y2.fs_out = fsB;
+  y2.fs_in = npts;
+  y2.fs_out = NZ;
+  y2.in_bytes = x1.dst_bytes;
   y2.os_in = NY;
   y2.ls_in = NXH * NY;
   y2.ps_in = 1;
   y2.ob_out = NY * csB;
   y2.ls_out = 1;
   y2.ps_out = (int)csB;
+  // (a kx plane of layout B; y and z lines that fit the LDS keep it below a third of 4 GiB)
   y2.out_bytes = (uint32_t)(((NY - 1) * csB + NZ) * (i64)sizeof(cx<T>));
   y2.n = NY;
   y2.nl = p->nl_y;
@@ -950,13 +907,13 @@ void build_step(psatd_plan* p, const StepIO& io, StepParams<T>& sp) {
     y2.pnl_sh = log2_of(y2.pnl);
     y2.pthreads = pair_block(y2.pnl, y2.pair.ra);
   }
-  set_slab_fwd(y2, p, 0, NZ);
+  y2.u_hi = NZ;
+  set_ypass(y2, 11);
 
   ZPushParams<T>& z3 = sp.z3;
   z3 = ZPushParams<T>{};
   z3.b = B;
   z3.npts = npts;
-  z3.fsB = fsB;
   z3.csB = csB;
   z3.coef = (const T*)p->coef;
   z3.coef_bytes = (uint32_t)(npts * (long long)sizeof(T));
@@ -1003,13 +960,15 @@ void build_step(psatd_plan* p, const StepIO& io, StepParams<T>& sp) {
 
   YPassParams<T>& y4 = sp.y4;
   y4 = YPassParams<T>{};
-  y4.in = B;
+  y4.in = B + io.z_lo;
   y4.out = A;
-  y4.fs_in = fsB;
+  y4.fs_in = NZ;
+  y4.fs_out = (i64)nzi * NXH * NY;
   y4.ob_in = NY * csB;
   y4.ls_in = 1;
   y4.ps_in = (int)csB;
-  y4.in_bytes = y2.out_bytes;
+  y4.in_bytes = y2.out_bytes - (uint32_t)(io.z_lo * (int)sizeof(cx<T>));
+  y4.out_bytes = (uint32_t)(y4.fs_out * (i64)sizeof(cx<T>));
   y4.os_out = NY;
   y4.ls_out = NXH * NY;
   y4.ps_out = 1;
@@ -1023,7 +982,8 @@ void build_step(psatd_plan* p, const StepIO& io, StepParams<T>& sp) {
   y4.pnl = y2.pnl;
   y4.pnl_sh = y2.pnl_sh;
   y4.pthreads = y2.pthreads;
-  set_slab_inv(y4, p, io.z_lo, io.z_hi - io.z_lo);
+  y4.u_hi = nzi;
+  set_ypass(y4, 6);
 
   XInvParams<T>& x5 = sp.x5;
   x5 = XInvParams<T>{};
@@ -1067,7 +1027,12 @@ void build_step(psatd_plan* p, const StepIO& io, StepParams<T>& sp) {
   }
   x5.ytiles = (io.y_hi - io.y_lo + x5.ty - 1) / x5.ty;
   x5.fd_ytiles = make_fastdiv(x5.ytiles);
-  set_slab(x5, io.z_lo, io.z_hi - io.z_lo);
+  x5.zfirst = io.z_lo;
+  x5.nzs = nzi;
+  x5.fd_nz = make_fastdiv(nzi);
+  x5.npts = y4.fs_out;
+  x5.src_bytes = y4.out_bytes;
+  x5.ntiles = 6 * nzi * x5.ytiles;
 }
 
 // Calls f(integral_constant<class>) for the pair class of an axis.
@@ -1173,7 +1138,7 @@ int run_pml(psatd_plan* p, const StepIO& io, void* const* parts, hipStream_t s) 
       for (int f = 0; f < 6; ++f) sp.x5.dst[f] = (T*)parts[6 * set + f];
     }
     YPassParams<T> y4 = sp.y4;
-    y4.in += (i64)6 * set * b_field_stride(p);
+    y4.in += (i64)6 * set * p->NZ;
     launch_p24<T>(y4, 1, p->pair[1].cls, s);
     launch_p5<T>(sp.x5, p->pair[0].cls, s);
     if (!fused) launch_pml_update(parts + 6 * set, p->pml_inc, p->pml_damp, set + 1, p->NX, p->NY, p->NZ, p->fp64, s);
