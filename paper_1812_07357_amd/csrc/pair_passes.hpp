@@ -72,15 +72,16 @@ __device__ __forceinline__ void pair_xfwd_body(const Src& S) {
     {
       const int c = fdiv(tid, P.fb), j = tid - c * RB;
       const int ya = ybase + 2 * c;
-      // lines past the last row are left out (nothing of them is stored)
-      const bool active = c < nc && ya < NY, hasb = ya + 1 < NY;
-      int ra = ya, rb = ya + 1;
+      // Lines past the last row are left out (nothing of them is stored).  The last row of an odd NY is its own
+      // partner: a row of zeros would take a select after each load (P1 of 576x320x320 FP32 0.918 -> 0.930
+      // ms, of 128-point lines 25.6 -> 28.1 us), and kOOB with a column added wraps back into the array.
+      const bool active = c < nc && ya < NY;
+      int ra = ya, rb = min(ya + 1, NY - 1);
       if (p.gather) {
-        ra = fmod_i(p.y0 + ya, p.fd_GY);
-        rb = fmod_i(p.y0 + ya + 1, p.fd_GY);
+        ra = fmod_i(p.y0 + ra, p.fd_GY);
+        rb = fmod_i(p.y0 + rb, p.fd_GY);
       }
-      const uint32_t oa = (uint32_t)((zrow + ra) * rowlen);
-      const uint32_t ob = hasb ? (uint32_t)((zrow + rb) * rowlen) : 0u, floor_b = hasb ? 0u : kOOB;
+      const uint32_t oa = (uint32_t)((zrow + ra) * rowlen), ob = (uint32_t)((zrow + rb) * rowlen);
       const rsrc_t src = make_rsrc(p.src[f], p.src_bytes);
       rsrc_t add = src;
       if constexpr (PML) add = make_rsrc(p.add[f < 6 ? f : 0], f < 6 ? p.src_bytes : 0u);
@@ -90,24 +91,13 @@ __device__ __forceinline__ void pair_xfwd_body(const Src& S) {
         else
           return gm<T>::ld(src, i);
       };
-      // The row past an odd NY is zero.  (kOOB with a column added would wrap back into the array.)  The
-      // large radices have no registers to spare for a select after the load (FP32, 768 points: P1 80
-      // against 71 us this way); the small ones are faster with it (147 points: 39 against 42 us).
-      auto load_b = [&](uint32_t i) PSATD_INLINE {
-        if constexpr (CLASS % 2 == 1) {
-          return load(max(i, floor_b));
-        } else {
-          const T v = load(i);
-          return hasb ? v : T(0);
-        }
-      };
       const int* xo = xoff + j;
       const int cb = fdiv(tid, P.fa), kb = tid - cb * RA;
       if constexpr (chirp_class(CLASS)) {
         chirp_stage_a<CLASS, -1, false>(lds, P, c, j, active, [&](auto, int t) PSATD_INLINE {
           const bool in = j + RB * t < N;
           const uint32_t xs = in ? (uint32_t)xo[RB * t] : 0u;
-          return cx<T>{load(in ? oa + xs : kOOB), load_b(in ? ob + xs : kOOB)};
+          return cx<T>{load(in ? oa + xs : kOOB), load(in ? ob + xs : kOOB)};
         });
         __syncthreads();
         chirp_stage_b<CLASS, -1>(lds, tw, P, cb, kb, cb < nc);
@@ -118,7 +108,7 @@ __device__ __forceinline__ void pair_xfwd_body(const Src& S) {
       } else {
         pair_stage_a<CLASS, -1, false>(lds, P, c, j, active, [&](auto, int t) PSATD_INLINE {
           const uint32_t xs = (uint32_t)xo[RB * t];
-          return cx<T>{load(oa + xs), load_b(ob + xs)};
+          return cx<T>{load(oa + xs), load(ob + xs)};
         });
         __syncthreads();
         pair_stage_b<CLASS, -1, true>(lds, tw, P, cb, kb, cb < nc, [&](int t, cx<T> v) PSATD_INLINE {
