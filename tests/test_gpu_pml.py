@@ -152,3 +152,18 @@ def test_z_lines_of_which_eleven_fit_the_lds_but_not_twelve(lib, interior, width
     """FP64 z pairs that the step's z pass takes and the one with the split increments cannot: direct
     (800) and chirp-z (380 and 344: 32 * 24 padded points)."""
     test_pml_steps_match_oracle(lib, "fp64", interior, 0, 8, widths)
+
+
+@pytest.mark.parametrize("precision", ["fp64", "fp32"])
+@pytest.mark.parametrize("interior,widths", [((245, 7, 6), (20, 1, 1)), ((6, 5, 245), (1, 1, 30)), ((5, 245, 6), (0, 25, 1)),
+                                              ((245, 3, 245), (9, 0, 11)), ((6, 5, 125), (1, 0, 12))])
+def test_axes_without_a_pair(lib, precision, interior, widths):
+    """245 = 5 * 7 * 7 runs on the Stockham kernels: along x the sum of the parts and the damped update are
+    kernels of their own over full fields and increments, along z the Stockham pass writes the twelve fields."""
+    plan = lib.Plan(*interior, nguard=0, order=8, precision=precision)
+    passes = plan.query(lib.Q_TWO_STAGE)
+    plan.close()
+    for axis, bit in ((0, 0), (1, 1), (2, 2)):
+        if interior[axis] == 245:
+            assert not passes >> bit & 1
+    test_pml_steps_match_oracle(lib, precision, interior, 0, 8, widths)
