@@ -33,8 +33,8 @@ FLAGS = [
 
 # Chirp-z lines: their zero padding folds out of the butterflies where -0 and +0 are the same value, which
 # they are for a field.  The Stockham y pass spills more with the flag (FP32, chirp-z lines of 579 to 645 points
-# 17 % slower), the direct pairs gain nothing.  (A kernel and its form for batches are compiled alike: their
-# results are the same bit for bit.)
+# 17 % slower), the direct pairs gain 2 % of one pass.  (A kernel and its form for batches are compiled alike:
+# their results are the same bit for bit.)
 _CHIRP_FLAGS = ["-fno-signed-zeros"]
 # (source, object name, extra flags).  passes.hip is compiled once per unit and precision, the
 # pair kernels (units 7..9) also once per pass, those of batches per class, so that the large pass

@@ -369,8 +369,9 @@ struct DepPtrs {
   int* list;    // n particle indices, tile by tile
 };
 
-__global__ void k_zero_int(int* a, int n) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
+// (Indices of tiles are unsigned where they step past the last one: a grid may have almost 2^31.)
+__global__ void k_zero_int(int* a, unsigned n) {
+  const unsigned i = blockIdx.x * blockDim.x + threadIdx.x;
   if (i < n) a[i] = 0;
 }
 
@@ -469,17 +470,18 @@ __global__ void __launch_bounds__(kTileThreads) k_tile_count(PicArgs<T> a, DepPt
 // Exclusive scan of the tile counts by one workgroup (offset[ntiles] = n); cursors start at the
 // offsets.  Four counts per thread and round, the next round's loaded before this one is summed
 // (65536 tiles: 0.152 -> 0.048 ms; the threads walked ranges of their own before).
-__global__ void __launch_bounds__(1024) k_tile_scan(const int* count, int* offset, int* cursor, int ntiles) {
+__global__ void __launch_bounds__(1024) k_tile_scan(const int* count, int* offset, int* cursor, unsigned ntiles) {
   __shared__ int wsum[2][16];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   int next[4], carry = 0;
-  auto load = [&](int i0) {
+  auto load = [&](unsigned i0) {
 #pragma unroll
-    for (int k = 0; k < 4; ++k) next[k] = i0 + k < ntiles ? count[i0 + k] : 0;
+    for (unsigned k = 0; k < 4; ++k) next[k] = i0 + k < ntiles ? count[i0 + k] : 0;
   };
   load(tid * 4);
-  for (int base = 0, par = 0; base < ntiles; base += 4096, par ^= 1) {
-    const int i0 = base + tid * 4;
+  int par = 0;
+  for (unsigned base = 0; base < ntiles; base += 4096, par ^= 1) {
+    const unsigned i0 = base + tid * 4;
     int c[4];
 #pragma unroll
     for (int k = 0; k < 4; ++k) c[k] = next[k];
@@ -501,7 +503,7 @@ __global__ void __launch_bounds__(1024) k_tile_scan(const int* count, int* offse
       carry += v;
     }
 #pragma unroll
-    for (int k = 0; k < 4; ++k) {
+    for (unsigned k = 0; k < 4; ++k) {
       if (i0 + k < ntiles) {
         offset[i0 + k] = run;
         cursor[i0 + k] = run;
@@ -683,7 +685,8 @@ __global__ void __launch_bounds__(kDepositThreads<K>) k_deposit_tiles(PicArgs<T>
   // merge walk: thread (row r0, column lx) of R = blockDim / E rows per round
   const int R = blockDim.x / E, r0 = tid / E, lx = tid - r0 * E;
   const int dy = R % E, dz = (R / E) % E, df = R / (E * E);
-  for (int t = blockIdx.x; t < a.ntiles; t += gridDim.x) {
+  for (unsigned next = blockIdx.x; next < (unsigned)a.ntiles; next += gridDim.x) {
+    const int t = (int)next;
     const int tz = t / (a.tx * a.ty), rem = t - tz * a.tx * a.ty, ty = rem / a.tx, tx = rem - ty * a.tx;
     const int bx = tx * a.tile, by = ty * a.tile, bz = tz * a.tile;
     for (int i = tid; i < 5 * ncl; i += blockDim.x) lds[i] = 0;
