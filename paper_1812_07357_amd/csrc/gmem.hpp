@@ -59,8 +59,7 @@ struct gm<float> {
   static __device__ __forceinline__ void stc_if(rsrc_t r, bool ok, uint32_t i, uint32_t so, cx<float> v) {
     __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, v), r, ok ? i * 8u : 0xfffffff8u, (int)so, 0);
   }
-  // complex elements i and i + 1 in one 16-byte load (8-byte aligned); with i past the array b may be any
-  // element of it
+  // complex elements i and i + 1 in one 16-byte load (8-byte aligned)
   static __device__ __forceinline__ void ldc2(rsrc_t r, uint32_t i, cx<float>& a, cx<float>& b) {
     const u32x4 w = __builtin_amdgcn_raw_buffer_load_b128(r, i * 8u, 0, 0);
     a = {__uint_as_float(w[0]), __uint_as_float(w[1])};

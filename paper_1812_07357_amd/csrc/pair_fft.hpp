@@ -196,7 +196,7 @@ __device__ __forceinline__ void pair_stage_b(const cx<T>* lds, const Tw<T>* tw, 
 
 // Chirp-z: point j + RB t of the line times the chirp, stage A.  With n <= (m + 1) / 2 and RA even
 // the points of t >= RA / 2 lie past the line: they are zeros of the code, and the DFT is
-// cut accordingly.  load(radix constant, t) is asked for t < RA / 2 only and must give zero from n on.
+// cut accordingly.  load(radix constant, t) is asked for t < RA / 2 only; from n on it may give any finite value (the chirp is zero).
 template <int CLASS, int S, bool LDSIN, typename T, typename Load>
 __device__ __forceinline__ void chirp_stage_a(cx<T>* lds, const PairFFT<T>& P, int line, int j, bool active,
                                               Load&& load) {

@@ -382,14 +382,24 @@ __device__ __forceinline__ void pair_xinv_body(const Src& S) {
       const int ya = ybase + 2 * c;
       const rsrc_t src = make_rsrc(p.src + (i64)f * p.npts, p.src_bytes);
       const bool hasa = ya < p.y_hi, hasb = ya + 1 < p.y_hi;
+      // Without a mask the compiler takes a load when its point is needed: fewer registers (FP32 150 -> 104,
+      // 223 -> 149 for the large radices) and more wavefronts, P5 of 288 points 23.9 -> 22.0 us, of 600 points
+      // 46 -> 38.  The large radices in FP64 have one wavefront per SIMD either way and want their loads in flight
+      // together, which the mask brings about (1056 points: 200 us, without it 288).
+      constexpr bool kMasked = sizeof(T) == 8 && CLASS == 1;
       const uint32_t base = (uint32_t)(zs * NXH * NY + ya);
       auto load = [&](auto, int t) PSATD_INLINE {
+        // Chirp-z points past the line read bin 0 of their own rows (the chirp is zero there); lines past
+        // the interior read whatever follows, and nothing of them is stored.
         const int i = j + RB * t;
-        const bool up = 2 * i > N, in = hasa && (!chirp_class(CLASS) || i < N);
-        const int kx = up ? N - i : i;
+        const bool up = 2 * i > N;
+        const int kx = up ? (chirp_class(CLASS) ? max(N - i, 0) : N - i) : i;
         cx<T> x, y;
-        gm<T>::ldc2(src, in ? base + __umul24((uint32_t)kx, (uint32_t)NY) : kOOB, x, y);
-        if (!(chirp_class(CLASS) ? in && hasb : hasb)) y = {T(0), T(0)};  // the row past an odd interior; past the line
+        if constexpr (kMasked)
+          gm<T>::ldc2(src, hasa ? base + __umul24((uint32_t)kx, (uint32_t)NY) : kOOB, x, y);
+        else
+          gm<T>::ldc2(src, base + __umul24((uint32_t)kx, (uint32_t)NY), x, y);
+        if (!hasb) y = {T(0), T(0)};  // the row past an odd interior
         // +1, -1 for the conjugate, 0 where the bin is its own conjugate (imaginary part dropped)
         const T s = (i == 0 || 2 * i == N) ? T(0) : (up ? T(-1) : T(1));
         return cx<T>{x.re - s * y.im, y.re + s * x.im};
