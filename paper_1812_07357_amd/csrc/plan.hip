@@ -1413,9 +1413,11 @@ float time_axis(psatd_plan* p, int ax, int reps, hipStream_t s) {
   StepIO io{};
   io.wsA = p->wsA;
   io.wsB = p->wsB;
-  T* scratch = (T*)p->wsB;  // box-shaped real arrays for P1 inputs / P5 outputs
-  for (int f = 0; f < 11; ++f) io.src[f] = scratch;
-  for (int f = 0; f < 6; ++f) io.dst[f] = scratch;
+  // box-shaped real arrays for P1 inputs / P5 outputs, each of its own like a step's: from one array for
+  // all fields P1 read the caches, and 32 * 18 points were taken for 24 * 24 (576x320x320: 4.09 against 4.04 ms)
+  T* scratch = (T*)p->wsB;
+  for (int f = 0; f < 11; ++f) io.src[f] = scratch + (size_t)f * p->ncell;
+  for (int f = 0; f < 6; ++f) io.dst[f] = scratch + (size_t)f * p->ncell;
   io.src_elems = io.dst_elems = p->ncell;
   io.y_lo = 0;
   io.y_hi = p->NY;
