@@ -156,8 +156,9 @@ __device__ __forceinline__ void pair_put(cx<T>* y, int pb, const cx<T>* v) {
 }
 
 // Stage A of butterfly (line, j): load(radix constant, t) gives point j + RB t of the line.  LDSIN: the points
-// come from the natural-order LDS line itself (a barrier between the reads and the writes).
-template <int CLASS, int S, bool LDSIN, typename T, typename Load>
+// come from the natural-order LDS line itself (a barrier between the reads and the writes).  AHEAD: from that
+// many points on all loads are issued before the DFT begins (0: where the compiler places them).
+template <int CLASS, int S, bool LDSIN, int AHEAD = 0, typename T, typename Load>
 __device__ __forceinline__ void pair_stage_a(cx<T>* lds, const PairFFT<T>& P, int line, int j, bool active,
                                              Load&& load) {
   with_radix(P.ra, typename radices<CLASS>::a{}, [&](auto rc) PSATD_INLINE {
@@ -166,6 +167,7 @@ __device__ __forceinline__ void pair_stage_a(cx<T>* lds, const PairFFT<T>& P, in
     if (active) {
 #pragma unroll
       for (int t = 0; t < R; ++t) v[t] = load(rc, t);
+      if constexpr (AHEAD > 0 && R >= AHEAD) __builtin_amdgcn_sched_barrier(0);
       dft<R, S, T>::run(v);
     }
     if constexpr (LDSIN) __syncthreads();

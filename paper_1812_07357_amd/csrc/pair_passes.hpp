@@ -38,6 +38,14 @@ __device__ __forceinline__ Tw<T>* tables_after(cx<T>* lds, int lines, const Pair
 }
 
 // ------------------------------------------------------------------ P1
+// A block's tile waits for its own loads, and its LDS leaves nine wavefronts per CU to cover them.  Left to
+// itself the compiler takes a load when the DFT needs it.  With all loads first P1 of 576x320x320 takes 0.868
+// instead of 0.925 ms (kernels compiled for 24 * 24 alone: 0.844), lines of 180 to 1056 points up to 12 % less;
+// those up to 160 up to 5 % more (101 registers: four wavefronts per SIMD, not five).  Held to five
+// wavefronts (two registers spilled) the box takes 0.888 ms.  The same costs the large radices in FP64 up to
+// 36 %, the x inverse 5 %, the y passes in FP64 4 %.
+template <typename T, int CLASS>
+constexpr int kAhead = sizeof(T) == 4 ? 14 : 0;
 // PML: a full field is the sum of its two split parts, added as they are loaded (the sources have
 // one array: an empty buffer reads as zero).
 template <int CLASS, bool BATCH, bool PML, typename T, typename Src>
@@ -106,7 +114,7 @@ __device__ __forceinline__ void pair_xfwd_body(const Src& S) {
           lds[c * P.ld + j + RB * t] = v;
         });
       } else {
-        pair_stage_a<CLASS, -1, false>(lds, P, c, j, active, [&](auto, int t) PSATD_INLINE {
+        pair_stage_a<CLASS, -1, false, kAhead<T, CLASS>>(lds, P, c, j, active, [&](auto, int t) PSATD_INLINE {
           const uint32_t xs = (uint32_t)xo[RB * t];
           return cx<T>{load(oa + xs), load(ob + xs)};
         });
